@@ -79,6 +79,7 @@ FP64_PEAK_TFLOPS = 78.6            # FP64 (vector and matrix cores)
 
 KERNEL_SOURCES = ("paper_1910_09534_amd/csrc/sv_device.h", "paper_1910_09534_amd/csrc/sv_kernels.hip",
                   "paper_1910_09534_amd/csrc/sv_mfma.hip", "paper_1910_09534_amd/csrc/sv_stage.hip",
+                  "paper_1910_09534_amd/csrc/sv_split.hip",
                   "paper_1910_09534_amd/csrc/sv_internal.h")
 TRAFFIC_FILE = "profiles/staged_pass_30q_d14_traffic.json"
 BATCH_TUNED = "profiles/batch_256_circuits_tuned.json"
@@ -533,7 +534,7 @@ def main(argv=None) -> int:
                         "frac": round(issued / ipeak, 4)},
              "traffic": counter_traffic(kind, p["bytes"] / p["count"])}
         if kind == "staged" and fp16:
-            r.update({"kernel": "k_stage, split-fp16 form (staged pass: 2-8 dense 4/5-qubit blocks per HBM "
+            r.update({"kernel": "k_split (split-fp16 staged pass: 2-8 dense 4/5-qubit blocks per HBM "
                                 "pass, fp16 matrix cores)",
                       "bound": "hbm", "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS,
                       "unit": "GB/s", "frac": round(gbs / HBM_PEAK_GBS, 4)})
@@ -988,7 +989,7 @@ def bench_single(args) -> int:
             "config": {"workload": "30-qubit complex64 state (dense), one random unitary 5-qubit block at "
                                    "targets 0-4, 10-14 and 20-24", "n": n},
             "per_targets": res,
-            "roofline": {"bound": "hbm", "kernel": "k_stage<14> (one-block staged pass, split-fp16 form)",
+            "roofline": {"bound": "hbm", "kernel": "k_split<14> (one-block staged pass, split-fp16 form)",
                          "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                          "frac": round(gbs / HBM_PEAK_GBS, 4), "avg_launch_ms": round(avg, 4),
                          "bytes_per_launch": by,

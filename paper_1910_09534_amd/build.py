@@ -6,7 +6,11 @@ Every HIP source is compiled with packed-FP32 instructions disabled
 (-target-feature -packed-fp32-ops): the compiler then emits only scalar FP32
 VALU ops for complex64 arithmetic.  Matrix-core accumulators are kept in
 ordinary VGPRs (-amdgpu-mfma-vgpr-form): the epilogues then read results
-without accumulator-register moves and the kernels need fewer registers.
+without accumulator-register moves and the kernels need fewer registers.  Branches
+that every lane takes alike stay plain branches
+(-structurizecfg-skip-uniform-regions): rewritten as predicated chains they
+add paths that no wave takes, and the compiler then waits on those paths'
+memory operations (the staged pass waited for its stores).
 """
 from __future__ import annotations
 
@@ -23,7 +27,7 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-    "-mllvm", "-amdgpu-mfma-vgpr-form",
+    "-mllvm", "-amdgpu-mfma-vgpr-form", "-mllvm", "-structurizecfg-skip-uniform-regions",
     "-ffp-contract=fast", "-Wall", "-Wno-unused-result",
     "-I", os.path.join(ROOT, "include"),
 ]

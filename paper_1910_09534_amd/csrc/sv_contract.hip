@@ -20,7 +20,7 @@
 //                     one output per lane, a loop over K.
 #include <hip/hip_runtime.h>
 
-#include "sv_internal.h"
+#include "sv_device.h"
 
 namespace sv {
 
@@ -183,31 +183,6 @@ typedef uint32_t cu4 __attribute__((ext_vector_type(4)));
 typedef uint32_t cu2 __attribute__((ext_vector_type(2)));
 
 constexpr int kSRow = 16;                  // f16 per LDS row: the chunk's 16 k values
-
-// f16 pair (a, b), round to nearest
-// f16(a s), f16(b s), each rounded once (s is a power of two, so a s is
-// exact): the scale and the conversion in one mixed-precision fma
-__device__ __forceinline__ uint32_t cpk_hi(float a, float b, float s)
-{
-    uint32_t r;
-    asm("v_fma_mixlo_f16 %0, %1, %3, 0\n\t"
-        "v_fma_mixhi_f16 %0, %2, %3, 0"
-        : "=&v"(r)
-        : "v"(a), "v"(b), "v"(s));
-    return r;
-}
-
-// f16(a s - hi.lo), f16(b s - hi.hi): residuals formed exactly in the fma,
-// rounded once
-__device__ __forceinline__ uint32_t cpk_lo(float a, float b, float s, uint32_t hi)
-{
-    uint32_t r;
-    asm("v_fma_mixlo_f16 %0, %1, %3, -%4 op_sel_hi:[0,0,1]\n\t"
-        "v_fma_mixhi_f16 %0, %2, %3, -%4 op_sel:[0,0,1] op_sel_hi:[0,0,1]"
-        : "=&v"(r)
-        : "v"(a), "v"(b), "v"(s), "v"(hi));
-    return r;
-}
 
 // element offset in a part of the LDS chunk of row r, k-octet o (0, 1):
 // the two octets of a row swap places on every other group of four rows,

@@ -11,6 +11,67 @@ template <> struct Vec2<float> { using T = float2; };
 template <> struct Vec2<double> { using T = double2; };
 
 typedef float f4 __attribute__((ext_vector_type(4)));
+typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+
+// bits of x, in ascending order, onto the set bits of m (host and device)
+__host__ __device__ inline uint64_t spread_bits(uint64_t x, uint64_t m)
+{
+    uint64_t r = 0;
+    while (m && x) {
+        const uint64_t low = m & (~m + 1);
+        if (x & 1) r |= low;
+        x >>= 1;
+        m &= m - 1;
+    }
+    return r;
+}
+
+// ---- fp32 values as pairs of fp16 parts --------------------------------------
+// f16(a), f16(b) packed (low half a), rounded to nearest even
+__device__ __forceinline__ uint32_t pk_hi(float a, float b)
+{
+    typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+    const h2 v = {(_Float16)a, (_Float16)b};
+    return __builtin_bit_cast(uint32_t, v);
+}
+
+// f16(a - hi.lo), f16(b - hi.hi) packed: each residual is formed exactly in
+// fp32 inside the mixed-precision fma and rounded once to fp16
+__device__ __forceinline__ uint32_t pk_lo(float a, float b, uint32_t hi)
+{
+    uint32_t r;
+    asm("v_fma_mixlo_f16 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]\n\t"
+        "v_fma_mixhi_f16 %0, %1, -1.0, %3 op_sel:[1,0,0] op_sel_hi:[1,0,0]"
+        : "=&v"(r)
+        : "v"(hi), "v"(a), "v"(b));
+    return r;
+}
+
+// f16(a s), f16(b s), each rounded once (s is a power of two, so a s is
+// exact): the scale and the conversion in one mixed-precision fma
+__device__ __forceinline__ uint32_t cpk_hi(float a, float b, float s)
+{
+    uint32_t r;
+    asm("v_fma_mixlo_f16 %0, %1, %3, 0\n\t"
+        "v_fma_mixhi_f16 %0, %2, %3, 0"
+        : "=&v"(r)
+        : "v"(a), "v"(b), "v"(s));
+    return r;
+}
+
+// f16(a s - hi.lo), f16(b s - hi.hi): residuals formed exactly in the fma,
+// rounded once
+__device__ __forceinline__ uint32_t cpk_lo(float a, float b, float s, uint32_t hi)
+{
+    uint32_t r;
+    asm("v_fma_mixlo_f16 %0, %1, %3, -%4 op_sel_hi:[0,0,1]\n\t"
+        "v_fma_mixhi_f16 %0, %2, %3, -%4 op_sel:[0,0,1] op_sel_hi:[0,0,1]"
+        : "=&v"(r)
+        : "v"(a), "v"(b), "v"(s), "v"(hi));
+    return r;
+}
 
 // Spread group counter g over the non-target positions.
 template <int K>

@@ -105,7 +105,7 @@ inline bool dense_uses_mfma(int k, int nloc, int mfma_min_k)
 // is |0...0> and is not read (the pass writes every amplitude).  norm_out
 // (non-null): each workgroup writes the FP64 sum of |psi|^2 of the amplitudes
 // it wrote to norm_out[workgroup]; *norm_blocks receives the workgroup count
-// (at most 1024).  support: positions on which the state may be non-zero
+// (at most 2048).  support: positions on which the state may be non-zero
 // (every other bit of a non-zero amplitude's index is 0); only tiles whose
 // id bits lie on support positions are visited, the others hold zeros and
 // stay zero, and the tile is widened with support positions only.  garbage: the memory outside the support's reach is not zero,
@@ -116,8 +116,9 @@ inline bool dense_uses_mfma(int k, int nloc, int mfma_min_k)
 // one 512-lane workgroup per CU, tiles of 9..13 positions).
 int stage_lds_bytes(int t, int nops, const int* ks, int dtype = 0);
 // LDS budget of a tile of t positions (complex64: 80 KiB up to 13, two
-// workgroups per CU; 160 KiB at 14, one 512-lane workgroup per CU;
-// complex128: 160 KiB).
+// workgroups per CU; 160 KiB at 14, one workgroup per CU; complex128:
+// 160 KiB).  The sizes are those of the fp32 form's padded tiles; the split
+// form's take no more.
 int stage_lds_limit(int t, int dtype = 0);
 // Sets the staged kernels' LDS attribute for every tile width (idempotent;
 // launch_stage does it on first use, graph capture needs it beforehand).
@@ -133,6 +134,14 @@ hipError_t launch_stage(hipStream_t st, void* psi, int nloc, int nops, const int
                         int* t_out, uint64_t support = ~0ull, bool garbage = false,
                         uint64_t* tile_mask_out = nullptr, uint64_t* amps_out = nullptr,
                         int split_exp = kNoSplit, int dtype = 0);
+// The split-fp16 form of a staged pass (sv_split.hip), called by launch_stage
+// with the tile chosen: positions P[0..t), the tiles' mask over the other
+// positions, newmask = the tile positions whose elements are zero but may
+// hold older values.  split_prepare: LDS attribute of a tile width's kernels.
+hipError_t launch_split(hipStream_t st, void* psi, int t, const int* P, int nops, const int* ks,
+                        const int* const* pos, const void* const* mats, uint64_t tiles, uint64_t tmask,
+                        uint64_t newmask, bool from_e0, double* norm_out, int* norm_blocks, int split_exp);
+hipError_t split_prepare(int t, int lds);
 // Exponent e of the split-fp16 form's tile scale 2^e for a run whose
 // blocks are all unitary and whose state norm stays below bound: the
 // largest e with 2^e bound <= 2^15 (-100..100); kNoSplit when bound is not
