@@ -418,8 +418,8 @@ const char* sv_batch_error(sv_batch b);
  *   accuracy, each tensor scaled by a power of two from its largest
  *   |component| and every value split into two fp16 parts, with two 8-byte
  *   words of stream-ordered device memory for the scales; | SV_CONTRACT_FP32
- *   for the 3M form on the fp32 matrix cores) or SV_C128 (FP64 sums).  All
- *   buffers 16-byte aligned.
+ *   for the 3M form on the fp32 matrix cores; below those sizes in FP32) or
+ *   SV_C128 (FP64 sums).  All buffers 16-byte aligned.
  *   hip_stream: stream to run on (NULL: the null stream); asynchronous.
  *   Errors: SV_EINVAL (NULL or misaligned buffer, e above 30, n1 + n2, n1 + e
  *   or n2 + e above 40, overlap), SV_EDEVICE; the text is last_error(NULL). */

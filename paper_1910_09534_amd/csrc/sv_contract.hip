@@ -16,8 +16,11 @@
 //                     re = P1 - P2, im = P3 - P1 - P2) on v_mfma_f32_16x16x4f32,
 //                     K in chunks of 16 through double-buffered LDS, the next
 //                     chunk's global loads in flight during the products.
-//   k_contract_plain  any size, complex64 (FP32 sums) or complex128 (FP64):
-//                     one output per lane, a loop over K.
+//   k_contract_full   complex128, and complex64 below those sizes, from 16 x 16
+//                     outputs and K = 4: four real products in the data's own
+//                     precision.
+//   k_contract_plain  what is left (an output side below 16, K below 4): one
+//                     output per lane, a loop over K.
 #include <hip/hip_runtime.h>
 
 #include "sv_device.h"
@@ -363,6 +366,175 @@ __global__ __launch_bounds__(kCThreads) void k_contract_split(const float2* t1, 
             }
 }
 
+// ---- full-precision matrix-core form ----------------------------------------
+// complex128 on v_mfma_f64_16x16x4f64 and the complex64 shapes that are too
+// small for the tiles above on v_mfma_f32_16x16x4f32: four real products
+// (Re = Br Ar - Bi Ai, Im = Br Ai + Bi Ar) in the precision of the data, so
+// the sums are those of k_contract_plain in another order.  A wave owns
+// 16 RB x 16 CB outputs and takes its operands straight from memory (16 lanes
+// read 16 consecutive elements): a step of four k for 2 x 2 blocks is 16
+// products, 1,024 matrix-core cycles in FP64, against four loads per lane, so
+// LDS would save little.  With one block a step is shorter than a load takes:
+// KU = 4 steps are loaded ahead at a time, and the SK waves of a workgroup
+// take a part of the sum each, added in LDS in a fixed order.
+template <typename T>
+struct Full;
+template <>
+struct Full<double> {
+    using V = double2;
+    typedef double acc __attribute__((ext_vector_type(4)));
+    static __device__ __forceinline__ acc mma(double a, double b, acc c)
+    {
+        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+    }
+    // row of result item v of lane group g
+    static __device__ __forceinline__ int row(int g, int v) { return g + 4 * v; }
+};
+template <>
+struct Full<float> {
+    using V = float2;
+    typedef float acc __attribute__((ext_vector_type(4)));
+    static __device__ __forceinline__ acc mma(float a, float b, acc c)
+    {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+    }
+    static __device__ __forceinline__ int row(int g, int v) { return 4 * g + v; }
+};
+
+template <typename T, int RB, int CB, int KU, int SK>
+__global__ __launch_bounds__(SK > 1 ? 64 * SK : 256) void k_contract_full(
+    const typename Full<T>::V* t1, const typename Full<T>::V* t2, typename Full<T>::V* __restrict__ out, int n1,
+    int n2, int e, uint32_t tiles_m, uint32_t tiles_n, uint32_t group)
+{
+    using F = Full<T>;
+    using V = typename F::V;
+    using acc = typename F::acc;
+    static_assert(SK == 1 || (RB == 1 && CB == 1), "the parts of a sum are added block by block");
+    const uint64_t N = 1ull << n1, M = 1ull << n2;
+    const uint32_t steps = (1u << (e - 2)) / SK;         // four k each
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    const int li = lane & 15, lk = lane >> 4;
+    // grouped order, as above: the waves of a workgroup share a t1 panel
+    const uint32_t wt = SK > 1 ? blockIdx.x : blockIdx.x * 4 + wave;
+    if (wt >= tiles_m * tiles_n) return;
+    const uint32_t per = group * tiles_n;
+    const uint32_t g = wt / per, r = wt % per;
+    const uint64_t m0 = (uint64_t)(g * group + r % group) * (16 * RB), n0 = (uint64_t)(r / group) * (16 * CB);
+    const uint64_t k0 = SK > 1 ? (uint64_t)wave * steps * 4 : 0;
+    const V* pb = t2 + (k0 + lk) * M + m0 + li;
+    const V* pa = t1 + (k0 + lk) * N + n0 + li;
+    acc re[RB][CB], im[RB][CB];
+#pragma unroll
+    for (int a = 0; a < RB; ++a)
+#pragma unroll
+        for (int b = 0; b < CB; ++b) re[a][b] = im[a][b] = acc{0, 0, 0, 0};
+    V nb[KU][RB], na[KU][CB];
+    auto load = [&](uint32_t s) {
+#pragma unroll
+        for (int u = 0; u < KU; ++u) {
+#pragma unroll
+            for (int a = 0; a < RB; ++a) nb[u][a] = pb[(uint64_t)(s + u) * 4 * M + 16 * a];
+#pragma unroll
+            for (int b = 0; b < CB; ++b) na[u][b] = pa[(uint64_t)(s + u) * 4 * N + 16 * b];
+        }
+    };
+    load(0);
+    for (uint32_t s = 0; s < steps; s += KU) {
+        V xb[KU][RB], xa[KU][CB];
+#pragma unroll
+        for (int u = 0; u < KU; ++u) {
+#pragma unroll
+            for (int a = 0; a < RB; ++a) xb[u][a] = nb[u][a];
+#pragma unroll
+            for (int b = 0; b < CB; ++b) xa[u][b] = na[u][b];
+        }
+        if (s + KU < steps) load(s + KU);
+        // the next steps' loads stay ahead of these products
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < KU; ++u) {
+#pragma unroll
+            for (int a = 0; a < RB; ++a)
+#pragma unroll
+                for (int b = 0; b < CB; ++b) {
+                    re[a][b] = F::mma(xb[u][a].x, xa[u][b].x, re[a][b]);
+                    im[a][b] = F::mma(xb[u][a].x, xa[u][b].y, im[a][b]);
+                }
+#pragma unroll
+            for (int a = 0; a < RB; ++a)
+#pragma unroll
+                for (int b = 0; b < CB; ++b) {
+                    re[a][b] = F::mma(-xb[u][a].y, xa[u][b].y, re[a][b]);
+                    im[a][b] = F::mma(xb[u][a].y, xa[u][b].x, im[a][b]);
+                }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    if constexpr (SK > 1) {
+        // item c = 2 v + {re, im} of lane l, one row of SK parts: lane l's
+        // items are added by threads l + 64 c (all of them in flight at once)
+        __shared__ T part[SK][8 * 64];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            part[wave][64 * (2 * v) + lane] = re[0][0][v];
+            part[wave][64 * (2 * v + 1) + lane] = im[0][0][v];
+        }
+        __syncthreads();
+        for (int i = threadIdx.x; i < 4 * 64; i += 64 * SK) {
+            const int l = i & 63, v = i >> 6;
+            T sr = 0, si = 0;
+#pragma unroll
+            for (int w = 0; w < SK; ++w) {
+                sr += part[w][64 * (2 * v) + l];
+                si += part[w][64 * (2 * v + 1) + l];
+            }
+            out[(m0 + F::row(l >> 4, v)) * N + n0 + (l & 15)] = V{sr, si};
+        }
+        return;
+    }
+#pragma unroll
+    for (int a = 0; a < RB; ++a)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+#pragma unroll
+            for (int b = 0; b < CB; ++b)
+                out[(m0 + 16 * a + F::row(lk, v)) * N + n0 + 16 * b + li] = V{re[a][b][v], im[a][b][v]};
+}
+
+template <typename T, int RB, int CB, int KU, int SK>
+hipError_t launch_full_tiles(hipStream_t st, const void* t1, const void* t2, void* out, int n1, int n2, int e)
+{
+    using V = typename Full<T>::V;
+    const uint64_t tm = (1ull << n2) / (16 * RB), tn = (1ull << n1) / (16 * CB);
+    if (tm * tn > 0xfffffff0ull) return hipErrorInvalidValue;
+    const uint32_t group = tm < 16 ? (uint32_t)tm : 16;
+    const uint64_t wgs = SK > 1 ? tm * tn : (tm * tn + 3) / 4;
+    hipLaunchKernelGGL((k_contract_full<T, RB, CB, KU, SK>), dim3((unsigned)wgs), dim3(SK > 1 ? 64 * SK : 256), 0, st,
+                       (const V*)t1, (const V*)t2, (V*)out, n1, n2, e, (uint32_t)tm, (uint32_t)tn, group);
+    return hipGetLastError();
+}
+
+// At least 16 x 16 outputs and four k.  32 x 32 outputs a wave where that
+// gives every SIMD one (1,024); 16 x 16 below, with the sum in 16 or 4 parts
+// while the outputs alone leave SIMDs idle and it is long enough to give each
+// wave four steps (2^18 outputs, e = 8: 20.6 us in one part, 22.7 in 16).
+// Measured (n1, n2, e; k_contract_plain -> here): complex128 12, 13, 6
+// 1,874 -> 325 us (53 TFLOP/s of 8 MNK), 12, 13, 10 28,852 -> 3,916 us (70, the
+// FP64 matrix product of the vendor's library reaches 73), 8, 8, 10 280 -> 19
+// us, 4, 4, 10 131 -> 17 us, 12, 12, 2 77 -> 49 us; complex64 12, 13, 3 260 ->
+// 56 us (4.8 TB/s, HBM), 6, 6, 8 40 -> 10 us.  64 x 32 outputs a wave need 408
+// registers in FP64, and 806 us at 12, 13, 6 when held to 256.
+template <typename T>
+hipError_t launch_full(hipStream_t st, const void* t1, const void* t2, void* out, int n1, int n2, int e)
+{
+    if (n2 >= 5 && n1 >= 5 && n1 + n2 >= 20) return launch_full_tiles<T, 2, 2, 1, 1>(st, t1, t2, out, n1, n2, e);
+    if (n1 + n2 <= 16 && e >= 8) return launch_full_tiles<T, 1, 1, 4, 16>(st, t1, t2, out, n1, n2, e);
+    if (n1 + n2 <= 17 && e >= 6) return launch_full_tiles<T, 1, 1, 4, 4>(st, t1, t2, out, n1, n2, e);
+    if (e >= 4) return launch_full_tiles<T, 1, 1, 4, 1>(st, t1, t2, out, n1, n2, e);
+    return launch_full_tiles<T, 1, 1, 1, 1>(st, t1, t2, out, n1, n2, e);
+}
+
 template <typename T, typename A>
 __global__ __launch_bounds__(256) void k_contract_plain(const T* __restrict__ t1, const T* __restrict__ t2,
                                                         T* __restrict__ out, int n1, int n2, int e)
@@ -424,6 +596,9 @@ hipError_t launch_contract(hipStream_t st, const void* t1, const void* t2, void*
                            (const float2*)t2, (float2*)out, n1, n2, e, (uint32_t)(1ull << (n1 - 6)), group);
         return hipGetLastError();
     }
+    if (n1 >= 4 && n2 >= 4 && e >= 2)
+        return dtype ? launch_full<double>(st, t1, t2, out, n1, n2, e)
+                     : launch_full<float>(st, t1, t2, out, n1, n2, e);
     const uint64_t total = 1ull << (n1 + n2);
     uint64_t grid = (total + 255) / 256;
     if (grid > (1u << 20)) grid = 1u << 20;

@@ -54,6 +54,31 @@ def test_contract_matches_oracle(n1, n2, e, dtype, fp32):
     assert orc.rel_l2(got, ref) <= (1e-13 if dtype == "c128" else 1e-5)
 
 
+@pytest.mark.parametrize("n1,n2,e", [(4, 4, 2), (5, 4, 3), (4, 7, 4), (6, 5, 7), (5, 6, 9), (4, 4, 8), (4, 14, 8),
+                                     (9, 11, 2), (5, 15, 5), (11, 11, 3)])
+@pytest.mark.parametrize("dtype", ["c64", "c128"])
+def test_contract_full_precision_tiles(n1, n2, e, dtype):
+    """The matrix-core form in the data's own precision (complex128, and
+    complex64 sizes outside the split form's): 16 x 16 outputs a wave with
+    one and four steps at a time, the sum in one, 4 and 16 parts, and 32 x 32.
+    The bound is that of a K-term sum of unit-size products, sqrt(K) eps
+    with a factor 4 for the complex product's four real sums."""
+    torch = _torch()
+    rng = np.random.default_rng(n1 * 1000 + n2 * 10 + e + 7)
+    ndt, eps = (np.complex64, 2.0 ** -24) if dtype == "c64" else (np.complex128, 2.0 ** -53)
+    t1 = _rand((1 << e) << n1, rng).astype(ndt)
+    t2 = _rand((1 << e) << n2, rng).astype(ndt)
+    g1, g2 = torch.from_numpy(t1).cuda(), torch.from_numpy(t2).cuda()
+    out = torch.full((1 << (n1 + n2),), complex(7.0, 7.0), dtype=g1.dtype, device="cuda")
+    sv.contract(g1.data_ptr(), g2.data_ptr(), out.data_ptr(), n1, n2, e, dtype,
+                torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    got = out.cpu().numpy().astype(np.complex128)
+    ref = D.contract_matrix(t1, t2, n1, n2, e)
+    bound = max(eps, 2.0 ** -52) * 4 * np.sqrt(1 << e)
+    assert orc.rel_l2(got, ref) <= bound, orc.rel_l2(got, ref)
+
+
 @pytest.mark.parametrize("s1,s2", [(1e-6, 1.0), (1.0, 3e5), (1e-15, 1e-12), (1e10, 1e-10)])
 def test_contract_split_accuracy_independent_of_scale(s1, s2):
     """The split-fp16 form scales each tensor from its own largest component:
