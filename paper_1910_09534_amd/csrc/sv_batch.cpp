@@ -110,6 +110,8 @@ hipError_t enqueue_all(sv_batch_s* b, const std::vector<Launch>& launches)
         hipError_t e = hipSuccess;
         if (L.kind == 0)
             e = launch_dense_batch(b->stream, L.dtype, L.k, L.fold, items + L.first, L.nitems, L.blocks);
+        else if (L.kind == 1 && L.dtype)
+            e = launch_dense64_mfma_batch(b->stream, L.k, L.fold, items + L.first, L.nitems, L.blocks);
         else if (L.kind == 1)
             e = launch_dense_mfma_batch(b->stream, L.k, L.fold, L.staged, items + L.first, L.nitems,
                                         L.blocks);
@@ -334,9 +336,9 @@ int sv_batch_prepare(int count, sv_handle* handles, int flags, void* hip_stream,
             }
             const int k = w.op->k;
             Sweep s = make_sweep(h->dev, h->n, k, w.op->pos, ab + w.op->off, w.fold ? &fd : nullptr, 0);
-            const bool mf = h->dtype == 0 && h->mfma_min_k >= 4 && k >= h->mfma_min_k && h->n >= k + 4;
-            // form: 0 VALU, 1 MFMA direct, 3 MFMA staged
-            groups[std::make_tuple(mf ? (s.staged ? 3 : 1) : 0, k, w.fold ? 1 : 0)].push_back(s);
+            const bool mf = h->dtype ? dense64_uses_mfma(k, h->n) : dense_uses_mfma(k, h->n, h->mfma_min_k);
+            // form: 0 VALU, 1 MFMA direct, 3 MFMA staged (complex64)
+            groups[std::make_tuple(mf ? (s.staged && !h->dtype ? 3 : 1) : 0, k, w.fold ? 1 : 0)].push_back(s);
             h->counters[0] += 1;
             h->counters[3] += (int64_t)1 << h->n;
         }

@@ -424,11 +424,13 @@ __global__ __launch_bounds__(SK > 1 ? 64 * SK : 256) void k_contract_full(
     const uint64_t k0 = SK > 1 ? (uint64_t)wave * steps * 4 : 0;
     const V* pb = t2 + (k0 + lk) * M + m0 + li;
     const V* pa = t1 + (k0 + lk) * N + n0 + li;
-    acc re[RB][CB], im[RB][CB];
+    // Br Ar, Bi Ai, Br Ai and Bi Ar are summed on their own: the rounding error
+    // of one sum of complex products, where one sum of both parts has 1.4 times it
+    acc rr[RB][CB], ii[RB][CB], ri[RB][CB], ir[RB][CB];
 #pragma unroll
     for (int a = 0; a < RB; ++a)
 #pragma unroll
-        for (int b = 0; b < CB; ++b) re[a][b] = im[a][b] = acc{0, 0, 0, 0};
+        for (int b = 0; b < CB; ++b) rr[a][b] = ii[a][b] = ri[a][b] = ir[a][b] = acc{0, 0, 0, 0};
     V nb[KU][RB], na[KU][CB];
     auto load = [&](uint32_t s) {
 #pragma unroll
@@ -458,15 +460,10 @@ __global__ __launch_bounds__(SK > 1 ? 64 * SK : 256) void k_contract_full(
             for (int a = 0; a < RB; ++a)
 #pragma unroll
                 for (int b = 0; b < CB; ++b) {
-                    re[a][b] = F::mma(xb[u][a].x, xa[u][b].x, re[a][b]);
-                    im[a][b] = F::mma(xb[u][a].x, xa[u][b].y, im[a][b]);
-                }
-#pragma unroll
-            for (int a = 0; a < RB; ++a)
-#pragma unroll
-                for (int b = 0; b < CB; ++b) {
-                    re[a][b] = F::mma(-xb[u][a].y, xa[u][b].y, re[a][b]);
-                    im[a][b] = F::mma(xb[u][a].y, xa[u][b].x, im[a][b]);
+                    rr[a][b] = F::mma(xb[u][a].x, xa[u][b].x, rr[a][b]);
+                    ii[a][b] = F::mma(xb[u][a].y, xa[u][b].y, ii[a][b]);
+                    ri[a][b] = F::mma(xb[u][a].x, xa[u][b].y, ri[a][b]);
+                    ir[a][b] = F::mma(xb[u][a].y, xa[u][b].x, ir[a][b]);
                 }
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -477,8 +474,8 @@ __global__ __launch_bounds__(SK > 1 ? 64 * SK : 256) void k_contract_full(
         __shared__ T part[SK][8 * 64];
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            part[wave][64 * (2 * v) + lane] = re[0][0][v];
-            part[wave][64 * (2 * v + 1) + lane] = im[0][0][v];
+            part[wave][64 * (2 * v) + lane] = rr[0][0][v] - ii[0][0][v];
+            part[wave][64 * (2 * v + 1) + lane] = ri[0][0][v] + ir[0][0][v];
         }
         __syncthreads();
         for (int i = threadIdx.x; i < 4 * 64; i += 64 * SK) {
@@ -499,7 +496,8 @@ __global__ __launch_bounds__(SK > 1 ? 64 * SK : 256) void k_contract_full(
         for (int v = 0; v < 4; ++v)
 #pragma unroll
             for (int b = 0; b < CB; ++b)
-                out[(m0 + 16 * a + F::row(lk, v)) * N + n0 + 16 * b + li] = V{re[a][b][v], im[a][b][v]};
+                out[(m0 + 16 * a + F::row(lk, v)) * N + n0 + 16 * b + li] =
+                    V{rr[a][b][v] - ii[a][b][v], ri[a][b][v] + ir[a][b][v]};
 }
 
 template <typename T, int RB, int CB, int KU, int SK>
@@ -520,11 +518,13 @@ hipError_t launch_full_tiles(hipStream_t st, const void* t1, const void* t2, voi
 // while the outputs alone leave SIMDs idle and it is long enough to give each
 // wave four steps (2^18 outputs, e = 8: 20.6 us in one part, 22.7 in 16).
 // Measured (n1, n2, e; k_contract_plain -> here): complex128 12, 13, 6
-// 1,874 -> 325 us (53 TFLOP/s of 8 MNK), 12, 13, 10 28,852 -> 3,916 us (70, the
+// 1,874 -> 316 us (54 TFLOP/s of 8 MNK), 12, 13, 10 28,852 -> 3,901 us (70, the
 // FP64 matrix product of the vendor's library reaches 73), 8, 8, 10 280 -> 19
-// us, 4, 4, 10 131 -> 17 us, 12, 12, 2 77 -> 49 us; complex64 12, 13, 3 260 ->
+// us, 4, 4, 10 131 -> 16 us, 12, 12, 2 77 -> 45 us; complex64 12, 13, 3 260 ->
 // 56 us (4.8 TB/s, HBM), 6, 6, 8 40 -> 10 us.  64 x 32 outputs a wave need 408
-// registers in FP64, and 806 us at 12, 13, 6 when held to 256.
+// registers in FP64, and 806 us at 12, 13, 6 when held to 256.  Relative error
+// against 80-bit sums: 2.0e-16 and 2.0e-16 (7, 8, 5), 2.8e-16 and 2.8e-16 (10,
+// 10, 6), 7.6e-16 and 2.4e-16 (5, 6, 9).
 template <typename T>
 hipError_t launch_full(hipStream_t st, const void* t1, const void* t2, void* out, int n1, int n2, int e)
 {

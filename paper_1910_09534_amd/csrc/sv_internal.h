@@ -37,6 +37,7 @@ struct Sweep {
     uint64_t lowmask[kMaxDense];   // (1 << p) - 1 for the target positions, ascending
     uint64_t block0;               // batched launches: first block of this sweep
     int tpos[kMaxDense];           // target positions in matrix-bit order
+    int asc[kMaxDense];            // matrix bits by ascending target position
     int k;
     int fold_m;
     int fold_pos[kMaxDiag];
@@ -88,6 +89,12 @@ hipError_t launch_dense_batch(hipStream_t st, int dtype, int k, bool fold, const
 hipError_t launch_dense_mfma_batch(hipStream_t st, int k, bool fold, bool staged, const Sweep* d_items,
                                    int nitems, uint64_t total_blocks);
 uint64_t mfma_batch_blocks(uint64_t groups);
+
+// complex128 blocks of k = 4, 5 on the FP64 matrix cores (nloc >= k + 4).
+inline bool dense64_uses_mfma(int k, int nloc) { return (k == 4 || k == 5) && nloc >= k + 4; }
+hipError_t launch_dense64_mfma(hipStream_t st, const Sweep& a);
+hipError_t launch_dense64_mfma_batch(hipStream_t st, int k, bool fold, const Sweep* d_items, int nitems,
+                                     uint64_t total_blocks);
 
 // Whether a complex64 k-qubit sweep over 2^nloc amplitudes runs on the
 // matrix cores (else on the vector units).

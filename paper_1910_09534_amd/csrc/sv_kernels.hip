@@ -191,6 +191,9 @@ Sweep make_sweep(void* psi, int nloc, int k, const int* pos, const void* mat, co
         }
     for (int j = 0; j < k; ++j) a.lowmask[j] = (1ull << sp[j]) - 1;
     for (int j = 0; j < k; ++j) a.tpos[j] = pos[j];
+    for (int u = 0; u < k; ++u)
+        for (int j = 0; j < k; ++j)
+            if (pos[j] == sp[u]) a.asc[u] = j;
     if (fold && fold->m > 0) {
         a.ftab = fold->table;
         a.fold_m = fold->m;
@@ -259,6 +262,7 @@ hipError_t launch_dense(hipStream_t st, void* psi, int dtype, int nloc, int k, c
     if (dtype == 0 && dense_uses_mfma(k, nloc, mfma_min_k))
         return launch_dense_mfma(st, psi, nloc, k, pos, mat, fold, idx_offset);
     const Sweep a = make_sweep(psi, nloc, k, pos, mat, fold, idx_offset);
+    if (dtype && dense64_uses_mfma(k, nloc)) return launch_dense64_mfma(st, a);
     if (dtype == 0) {
         switch (k) {
             case 1: return dense_dispatch<float, 1>(st, a);

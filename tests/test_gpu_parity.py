@@ -406,6 +406,35 @@ def test_sweep_profile_splits_kinds():
         sv.destroy_state(h)
 
 
+@pytest.mark.parametrize("n", [8, 9, 10, 14])
+@pytest.mark.parametrize("k", [4, 5])
+def test_dense64_matrix_core_sweep(n, k):
+    """complex128 blocks of 4 and 5 qubits as single sweeps: one unit of 16
+    groups in all (or too few: the vector form), a few, many; low, high and
+    mixed targets in any order, alone and with a folded diagonal.  A sum of
+    2^k products of a unitary's entries: 8 eps."""
+    rng = np.random.default_rng(100 * n + k)
+    for targets in (list(range(k)), list(range(n - k, n)), [int(x) for x in rng.choice(n, size=k, replace=False)]):
+        for diag in (None, (0, n - 1, n // 2)):
+            qs = [int(q) for q in rng.permutation(targets)]
+            psi = W.random_state(n, rng)
+            h, t = state_from_numpy(psi, "c128")
+            try:
+                sv.set_option(h, sv.SV_OPT_STAGE, 0)
+                u = W.random_unitary(1 << k, rng)
+                sv.apply_fused(h, qs, u, "c128")
+                ref = psi.copy()
+                orc.apply_dense(ref, qs, u)
+                if diag:
+                    ph = W.random_phases(8, rng)
+                    sv.apply_diag(h, diag, ph, "c128")
+                    orc.apply_diag(ref, list(diag), ph)
+                assert orc.rel_l2(read_all(h, n), ref) <= 8 * 2.0 ** -52, (qs, diag)
+                assert sv.counters(h)["dense_sweeps"] == 1 and sv.counters(h)["diag_sweeps"] == 0
+            finally:
+                sv.destroy_state(h)
+
+
 @pytest.mark.parametrize("first", ["staged", "single", "read"])
 def test_deferred_reset(first):
     """sv_reset defers writing |0...0>: a first staged pass builds its input
