@@ -406,6 +406,38 @@ def test_sweep_profile_splits_kinds():
         sv.destroy_state(h)
 
 
+@pytest.mark.parametrize("dtype", ["c64", "c128"])
+@pytest.mark.parametrize("n,sliced", [(1, 0), (2, 0), (7, 0), (8, 0), (9, 0), (10, 0), (14, 0), (14, 3), (11, 3)])
+def test_diag_positions(n, sliced, dtype):
+    """A diagonal gate on its own: positions inside an access (0), inside a
+    workgroup's chunk, above it and sliced, in any order, up to 12 of them;
+    states below and above one chunk.  One complex product per amplitude:
+    2 eps."""
+    rng = np.random.default_rng(1000 * n + sliced)
+    mask = ((1 << sliced) - 1) << (n - sliced)
+    sets = [[0], [n - 1], list(range(min(n, 12))), list(range(max(0, n - 12), n)),
+            [int(q) for q in rng.choice(n, size=max(1, min(n, 12) // 2), replace=False)]]
+    for qs in sets:
+        qs = [int(q) for q in rng.permutation(qs)]
+        st = sv.State(n, mask, dtype)
+        try:
+            psi = orc.zero_state(n)
+            for q in range(n - sliced):                  # every local amplitude non-zero
+                u = W.random_unitary(2, rng)
+                st.fused([q], u)
+                orc.apply_dense(psi, [q], u)
+            before = read_all(st.h, n)
+            ph = W.random_phases(1 << len(qs), rng)
+            st.diag(qs, ph)
+            got = read_all(st.h, n)
+            ref = before.copy()
+            orc.apply_diag(ref, qs, ph.astype(np.complex64) if dtype == "c64" else ph)
+            assert orc.rel_l2(got, ref) <= (2.0 ** -23 if dtype == "c64" else 2.0 ** -52), qs
+            assert sv.counters(st.h)["diag_sweeps"] == 1
+        finally:
+            st.close()
+
+
 @pytest.mark.parametrize("n", [8, 9, 10, 14])
 @pytest.mark.parametrize("k", [4, 5])
 def test_dense64_matrix_core_sweep(n, k):
