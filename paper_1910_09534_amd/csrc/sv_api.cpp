@@ -425,8 +425,22 @@ int run_ops(sv_state* h, hipStream_t st, void** psi, void* alt, int nloc, uint64
 
 int upload_arena(sv_state* h, const WorkBufs* wb = nullptr)
 {
-    const size_t bytes = h->arena.size();
+    size_t bytes = h->arena.size();
     if (bytes == 0) return SV_OK;
+    // a few small matrices travel in the launch that stores them: one launch
+    // instead of a copy, an event and the wait for it before the next queue
+    const size_t up = (bytes + 15) & ~(size_t)15;
+    if (up <= kUploadMax && !h->tier) {
+        if (wb && up > wb->arena_cap) return set_err(h, SV_EINVAL, "queued matrices exceed the work area");
+        if (!wb) {
+            const int rc = ensure_dev(h, &h->d_arena, &h->d_arena_cap, (size_t)1 << 20);
+            if (rc) return rc;
+        }
+        h->arena.resize(up);
+        h->d_arena_use = wb ? wb->arena : h->d_arena;
+        TRY(h, launch_upload(h->stream, (void*)h->d_arena_use, h->arena.data(), up));
+        return SV_OK;
+    }
     if (wb) {
         // caller-provided device memory; the copy reads the queue's own host
         // buffer, which nothing changes before the caller's call returns
@@ -926,6 +940,7 @@ void release(sv_state* h)
     for (const auto& w : work)
         if (w.first) pool_free(w.first, w.second, false);
     if (h->h_arena) pool_free(h->h_arena, h->h_arena_cap, true);
+    if (h->h_red) pool_free(h->h_red, h->h_red_cap, true);
     for (auto* v : {&h->ev_in, &h->ev_comp, &h->ev_out, &h->tev_pool})
         for (hipEvent_t e : *v) (void)hipEventDestroy(e);
     if (h->ev_arena) (void)hipEventDestroy(h->ev_arena);
@@ -1140,57 +1155,140 @@ int finish_sum(sv_state* h, hipStream_t st, const WorkBufs& w, int nblocks, int 
     return SV_OK;
 }
 
-int do_reduce(sv_state* h, const void* trailing, int64_t count, const uint64_t* bits, void* out,
-              double* stats, const WorkBufs* wb = nullptr)
+// T's columns as the physical slices multiply by them: tcols[t][r] =
+// T[r][rowmap[t]], rowmap[t] = physical slice id -> T index (bit i = i-th
+// sliced qubit in ascending label order).
+void slice_columns(const sv_state* h, const double* T, std::vector<int>& rowmap, std::vector<double>& tcols)
 {
-    CHECK_HANDLE(h);
-    if (count < 0 || (count > 0 && (!bits || !out))) return set_err(h, SV_EINVAL, "bad output arguments");
-    const uint64_t lim = h->n >= 64 ? ~0ull : ((1ull << h->n) - 1);
-    for (int64_t j = 0; j < count; ++j)
-        if (bits[j] > lim) return set_err(h, SV_EINVAL, "bitstring >= 2^n");
-    int rc;
     const int ns = 1 << h->s;
-    const size_t cnt = (size_t)std::max<int64_t>(count, 1);
-    WorkBufs w;
-    if (wb) {
-        w = *wb;
-    } else {
-        if ((rc = ensure_dev(h, &h->d_bits, &h->d_bits_cap, cnt * 8))) return rc;
-        if ((rc = ensure_dev(h, &h->d_acc, &h->d_acc_cap, cnt * 16))) return rc;
-        if ((rc = ensure_dev(h, &h->d_part, &h->d_part_cap, kPartDoubles * sizeof(double)))) return rc;
-        // T (all columns, gathered per physical slice) + per-slice norms
-        if ((rc = ensure_dev(h, &h->d_tcol, &h->d_tcol_cap, (size_t)ns * ns * 16 + (size_t)ns * 8))) return rc;
-        if ((rc = ensure_dev(h, &h->d_rowmap, &h->d_rowmap_cap, (size_t)ns * 4))) return rc;
-        w = WorkBufs{h->d_bits, h->d_acc, h->d_part, h->d_tcol, h->d_rowmap, h->d_small, nullptr, 0};
-    }
-
-    // logical bitstring -> physical index
-    std::vector<int> from(h->n), to(h->n);
-    for (int q = 0; q < h->n; ++q) { from[q] = q; to[q] = h->pos[q]; }
-    const BitRuns l2p = make_runs(h->n, from.data(), to.data());
-    // physical slice id -> T index (bit i = i-th sliced qubit in ascending label order)
     std::vector<int> sl;
     for (int q = 0; q < h->n; ++q)
         if (h->pos[q] >= h->L) sl.push_back(q);
-    std::vector<int> rowmap(ns);
+    rowmap.resize(ns);
     for (int t = 0; t < ns; ++t) {
         int r = 0;
         for (int i = 0; i < h->s; ++i)
             if ((t >> (h->pos[sl[i]] - h->L)) & 1) r |= 1 << i;
         rowmap[t] = r;
     }
-    const double* T = (const double*)trailing;
-    // tcols[t][r] = T[r][rowmap[t]]: the column a physical slice t multiplies
+    if (!T) return;
+    tcols.assign((size_t)ns * ns * 2, 0.0);
+    for (int t = 0; t < ns; ++t)
+        for (int r = 0; r < ns; ++r) {
+            const size_t src = 2 * ((size_t)r * ns + rowmap[t]);
+            tcols[2 * ((size_t)t * ns + r)] = T[src];
+            tcols[2 * ((size_t)t * ns + r) + 1] = T[src + 1];
+        }
+}
+
+// Resident states: the queue, then one launch that reads the bitstrings from
+// pinned memory and writes amplitudes and sums there (up to
+// kPinnedBitstrings; larger calls, and those that may not allocate, copy).
+constexpr int64_t kPinnedBitstrings = 1 << 17;
+
+int reduce_resident(sv_state* h, const double* T, int64_t count, const uint64_t* bits, void* out, double* stats,
+                    const BitRuns& l2p, const WorkBufs* wb)
+{
+    const int ns = 1 << h->s;
+    const size_t cnt = (size_t)std::max<int64_t>(count, 1);
+    const bool pinned = !wb && count <= kPinnedBitstrings;
+    hipStream_t st = h->stream;
+    int rc;
+    WorkBufs w;
+    if (wb) {
+        w = *wb;
+    } else {
+        if ((rc = ensure_dev(h, &h->d_part, &h->d_part_cap, kPartDoubles * sizeof(double)))) return rc;
+        if (!pinned) {
+            if ((rc = ensure_dev(h, &h->d_bits, &h->d_bits_cap, cnt * 8))) return rc;
+            if ((rc = ensure_dev(h, &h->d_acc, &h->d_acc_cap, cnt * 16))) return rc;
+        } else if (h->h_red_cap < 64 + cnt * 24) {
+            // (idle: every reduction waits for its results)
+            if (h->h_red) pool_free(h->h_red, h->h_red_cap, true);
+            h->h_red_cap = 0;
+            h->h_red = pool_alloc(64 + cnt * 24, true, &h->h_red_cap);
+            if (!h->h_red) return set_err(h, SV_ENOMEM, "pinned staging allocation failed");
+        }
+        if (T) {
+            if ((rc = ensure_dev(h, &h->d_tcol, &h->d_tcol_cap, (size_t)ns * ns * 16))) return rc;
+            if ((rc = ensure_dev(h, &h->d_rowmap, &h->d_rowmap_cap, (size_t)ns * 4))) return rc;
+        }
+        w = WorkBufs{h->d_bits, h->d_acc, h->d_part, h->d_tcol, h->d_rowmap, h->d_small, nullptr, 0};
+    }
+    std::vector<int> rowmap;
     std::vector<double> tcols;
     if (T) {
-        tcols.assign((size_t)ns * ns * 2, 0.0);
-        for (int t = 0; t < ns; ++t)
-            for (int r = 0; r < ns; ++r) {
-                const size_t src = 2 * ((size_t)r * ns + rowmap[t]);
-                tcols[2 * ((size_t)t * ns + r)] = T[src];
-                tcols[2 * ((size_t)t * ns + r) + 1] = T[src + 1];
-            }
+        slice_columns(h, T, rowmap, tcols);
+        TRY(h, hipMemcpyAsync(w.rowmap, rowmap.data(), (size_t)ns * 4, hipMemcpyHostToDevice, st));
+        TRY(h, hipMemcpyAsync(w.tcol, tcols.data(), tcols.size() * 8, hipMemcpyHostToDevice, st));
     }
+    if (!pinned && count > 0)
+        TRY(h, hipMemcpyAsync(w.bits, bits, (size_t)count * 8, hipMemcpyHostToDevice, st));
+    // the norm rides on the queue's last staged pass when it has one
+    int norm_blocks = 0;
+    rc = flush(h, stats ? (double*)w.part : nullptr, stats ? &norm_blocks : nullptr, wb);
+    if (rc) return rc;
+    if (stats && norm_blocks == 0)
+        TRY(h, launch_norm_partials(st, h->dev, h->dtype, h->n, (double*)w.part, &norm_blocks));
+    const uint64_t* bsrc = (const uint64_t*)w.bits;
+    double* adst = (double*)w.acc;
+    double* sdst = (double*)w.small;
+    if (pinned) {
+        sdst = (double*)h->h_red;
+        adst = (double*)((char*)h->h_red + 64);
+        uint64_t* hb = (uint64_t*)((char*)h->h_red + 64 + cnt * 16);
+        if (count > 0) std::memcpy(hb, bits, (size_t)count * 8);
+        bsrc = hb;
+    }
+    if (stats && !wb && !h->ticket_ready) {
+        const double zero[8] = {};
+        TRY(h, launch_upload(st, w.small, zero, sizeof(zero)));
+        h->ticket_ready = true;
+    }
+    TRY(h, launch_reduce(st, h->dev, h->dtype, h->L, ns, l2p, count, bsrc, T ? w.tcol : nullptr,
+                         (const int*)w.rowmap, adst, (double)h->n, (double*)w.part, norm_blocks,
+                         (unsigned*)((char*)w.small + kTicketAt), stats ? sdst : nullptr));
+    if (pinned) {
+        TRY(h, hipStreamSynchronize(st));
+        if (count > 0) std::memcpy(out, adst, (size_t)count * 16);
+        if (stats) std::memcpy(stats, sdst, 3 * sizeof(double));
+        return SV_OK;
+    }
+    if (count > 0) TRY(h, hipMemcpyAsync(out, adst, (size_t)count * 16, hipMemcpyDeviceToHost, st));
+    if (stats) TRY(h, hipMemcpyAsync(stats, sdst, 3 * sizeof(double), hipMemcpyDeviceToHost, st));
+    TRY(h, hipStreamSynchronize(st));
+    return SV_OK;
+}
+
+int do_reduce(sv_state* h, const void* trailing, int64_t count, const uint64_t* bits, void* out,
+              double* stats, const WorkBufs* wb = nullptr)
+{
+    CHECK_HANDLE(h);
+    if (count < 0 || (count > 0 && (!bits || !out))) return set_err(h, SV_EINVAL, "bad output arguments");
+    uint64_t any = 0;
+    for (int64_t j = 0; j < count; ++j) any |= bits[j];
+    if (h->n < 64 && (any >> h->n)) return set_err(h, SV_EINVAL, "bitstring >= 2^n");
+    // logical bitstring -> physical index
+    std::vector<int> from(h->n), to(h->n);
+    for (int q = 0; q < h->n; ++q) { from[q] = q; to[q] = h->pos[q]; }
+    const BitRuns l2p = make_runs(h->n, from.data(), to.data());
+    if (!h->tier) return reduce_resident(h, (const double*)trailing, count, bits, out, stats, l2p, wb);
+
+    // host tier: one pass over the slices accumulates them in turn
+    int rc;
+    const int ns = 1 << h->s;
+    const size_t cnt = (size_t)std::max<int64_t>(count, 1);
+    if ((rc = ensure_dev(h, &h->d_bits, &h->d_bits_cap, cnt * 8))) return rc;
+    if ((rc = ensure_dev(h, &h->d_acc, &h->d_acc_cap, cnt * 16))) return rc;
+    if ((rc = ensure_dev(h, &h->d_part, &h->d_part_cap, kPartDoubles * sizeof(double)))) return rc;
+    // T (all columns, gathered per physical slice) + per-slice norms
+    if ((rc = ensure_dev(h, &h->d_tcol, &h->d_tcol_cap, (size_t)ns * ns * 16 + (size_t)ns * 8))) return rc;
+    if ((rc = ensure_dev(h, &h->d_rowmap, &h->d_rowmap_cap, (size_t)ns * 4))) return rc;
+    const WorkBufs w{h->d_bits, h->d_acc, h->d_part, h->d_tcol, h->d_rowmap, h->d_small, nullptr, 0};
+    const double* T = (const double*)trailing;
+    std::vector<int> rowmap;
+    std::vector<double> tcols;
+    slice_columns(h, T, rowmap, tcols);
     hipStream_t st = h->stream;
     double* d_snorm = (double*)((char*)w.tcol + (size_t)ns * ns * 16);
     if (count > 0) {
@@ -1200,7 +1298,6 @@ int do_reduce(sv_state* h, const void* trailing, int64_t count, const uint64_t* 
     TRY(h, hipMemcpyAsync(w.rowmap, rowmap.data(), (size_t)ns * 4, hipMemcpyHostToDevice, st));
     if (T) TRY(h, hipMemcpyAsync(w.tcol, tcols.data(), tcols.size() * 8, hipMemcpyHostToDevice, st));
     TRY(h, hipMemsetAsync(d_snorm, 0, (size_t)ns * 8, st));
-    int folded_blocks = 0;
     // nothing below synchronises the host per slice: the tier pipeline keeps
     // staging the next slice while this one is reduced
     auto visit = [&](int t, const void* slice_buf) -> int {
@@ -1209,32 +1306,23 @@ int do_reduce(sv_state* h, const void* trailing, int64_t count, const uint64_t* 
                                  (const uint64_t*)w.bits, tc, (const int*)w.rowmap,
                                  (double*)w.acc));
         if (stats) {
-            int nb = folded_blocks;      // partials already written by the last staged pass
-            if (nb == 0)
-                TRY(h, launch_norm_partials(st, slice_buf, h->dtype, h->L, (double*)w.part, &nb));
+            int nb = 0;
+            TRY(h, launch_norm_partials(st, slice_buf, h->dtype, h->L, (double*)w.part, &nb));
             TRY(h, launch_finish_sum(st, (const double*)w.part, nb, 1, d_snorm + t));
         }
         return SV_OK;
     };
-    if (!h->tier) {
-        // unsliced: the norm rides on the queue's last staged pass when it has one
-        rc = (stats && ns == 1) ? flush(h, (double*)w.part, &folded_blocks, wb) : flush(h, nullptr, nullptr, wb);
+    // one pass over the tier: pending ops, then the reduction, then write back
+    const bool pending = !h->ops.empty();
+    if (pending) {
+        rc = upload_arena(h);
         if (rc) return rc;
-        for (int t = 0; t < ns && !rc; ++t)
-            rc = visit(t, (const char*)h->dev + ((size_t)t << h->L) * h->amp);
-    } else {
-        // one pass over the tier: pending ops, then the reduction, then write back
-        const bool pending = !h->ops.empty();
-        if (pending) {
-            rc = upload_arena(h);
-            if (rc) return rc;
-        }
-        rc = tier_pass(h, pending, visit);
-        if (rc) return rc;
-        h->ops.clear();
-        h->arena.clear();
-        if (h->timing) rc = collect_timing(h);
     }
+    rc = tier_pass(h, pending, visit);
+    if (rc) return rc;
+    h->ops.clear();
+    h->arena.clear();
+    if (h->timing) rc = collect_timing(h);
     if (rc) return rc;
     if (count > 0)
         TRY(h, hipMemcpyAsync(out, w.acc, (size_t)count * 16, hipMemcpyDeviceToHost, st));

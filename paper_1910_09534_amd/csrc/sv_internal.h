@@ -189,6 +189,28 @@ hipError_t launch_accumulate(hipStream_t st, const void* psi_slice, int dtype, i
                              const uint64_t* bits, const void* tcol, const int* rowmap,
                              double* acc);
 
+// The reduction of a resident state in one launch (all 2^s slices lie in psi,
+// slice t at t << nloc).  For j < count, phys = runs(x_j), r = rowmap(phys >>
+// nloc):
+//   out[j] = psi[phys]                                (tcols == nullptr)
+//   out[j] = sum_t tcols[t][r] psi[t << nloc | phys's low bits], t ascending
+// bits and out may be device or pinned host memory.  stats (non-null; device
+// or pinned host): [0] the sum of norm_count doubles at part[0..), [1], [2] the
+// sums of N |out_j|^2 and ln(N |out_j|^2), N = 2^logn, all in a fixed order;
+// part holds kPartDoubles doubles (the last kReducePart are its own), *ticket
+// is zero before and after.
+constexpr size_t kPartDoubles = 4096 * 2;    // FP64 partial sums of a reduction
+constexpr int kTicketAt = 32;                // k_reduce's ticket in the 64-byte work buffer
+constexpr int kReduceBlocks = 2048, kReducePart = 2 * kReduceBlocks;
+hipError_t launch_reduce(hipStream_t st, const void* psi, int dtype, int nloc, int ns, const BitRuns& log_to_phys,
+                         int64_t count, const uint64_t* bits, const void* tcols, const int* rowmap, double* out,
+                         double logn, double* part, int norm_count, unsigned* ticket, double* stats);
+
+// Device copy of a few bytes of host memory (a multiple of 16, at most
+// kUploadMax), carried in the launch itself: src may change on return.
+constexpr size_t kUploadMax = 3584;
+hipError_t launch_upload(hipStream_t st, void* dst, const void* src, size_t bytes);
+
 // Deterministic FP64 sum of |psi|^2 over 2^nloc amplitudes: writes
 // nblocks partial sums to partial (device), returns the block count used.
 hipError_t launch_norm_partials(hipStream_t st, const void* psi, int dtype, int nloc,

@@ -15,6 +15,8 @@
 // base + l); the group counter is spread over the non-target bit positions
 // in ascending order, so for targets above bit 5 the 64 lanes of one load
 // instruction read 64 consecutive amplitudes (512 B for complex64).
+#include <cstring>
+
 #include "sv_device.h"
 
 namespace sv {
@@ -641,20 +643,30 @@ __device__ __forceinline__ void block_tree(double (*sh)[256], double* v)
     for (int w = 0; w < W; ++w) v[w] = sh[w][0];
 }
 
+// Four 16-byte accesses per lane in flight: with one amplitude at a time a
+// state of 2^20 to 2^24 amplitudes waits for memory (15.5 us a state; here 5).
 template <typename R>
 __global__ __launch_bounds__(256) void k_norm(const typename Vec2<R>::T* __restrict__ psi,
                                               uint64_t per_block, double* __restrict__ partial)
 {
+    using V = typename Vec2<R>::T;
+    constexpr int E = 16 / sizeof(V);                    // amplitudes per access
+    typedef R A __attribute__((ext_vector_type(2 * E)));
     __shared__ double sh[1][256];
-    const uint64_t b0 = (uint64_t)blockIdx.x * per_block;
-    double s = 0.0;
-    for (uint64_t i = threadIdx.x; i < per_block; i += 256) {
-        const auto a = psi[b0 + i];
-        const double re = (double)a.x, im = (double)a.y;
-        s = fma(re, re, s);
-        s = fma(im, im, s);
+    const A* p = (const A*)(psi + (uint64_t)blockIdx.x * per_block);
+    const uint64_t count = per_block / E;
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    for (uint64_t i = threadIdx.x; i < count; i += 4 * 256) {
+        A x[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            x[u] = i + 256 * u < count ? p[i + 256 * u] : A{};
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int c = 0; c < 2 * E; ++c) s[u] = fma((double)x[u][c], (double)x[u][c], s[u]);
     }
-    double v[1] = {s};
+    double v[1] = {(s[0] + s[1]) + (s[2] + s[3])};
     block_tree<1>(sh, v);
     if (threadIdx.x == 0) partial[blockIdx.x] = v[0];
 }
@@ -724,6 +736,128 @@ hipError_t launch_finish_sum(hipStream_t st, const double* partial, int count, i
 {
     if (width < 1 || width > 2) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_finish, dim3(1), dim3(256), 0, st, partial, count, width, out);
+    return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
+// gather, cross-slice sum, cross-entropy sums and norm of a resident state
+// ---------------------------------------------------------------------------
+// One launch where there were six and four copies (k_accum per slice, k_xeb,
+// two k_finish, the cleared accumulators, the row map): on small states a
+// reduction is launches: 16 qubits, depth 8, complex128, 2^16 bitstrings take
+// 183 us with this and k_upload against 278, and a small diagonal gate with
+// k_upload alone 20.0 against 23.8.  The last workgroup to finish (a ticket that it resets) adds
+// the workgroups' partial sums, each in a fixed order.
+template <typename R>
+__global__ __launch_bounds__(256) void k_reduce(const typename Vec2<R>::T* __restrict__ psi, int nloc, int ns,
+                                                RunsK l2p, int64_t count, int64_t per,
+                                                const uint64_t* __restrict__ bits,
+                                                const double2* __restrict__ tcols, const int* __restrict__ rowmap,
+                                                double2* __restrict__ out, double logn, double* part,
+                                                int norm_count, unsigned* ticket, double* stats)
+{
+    __shared__ double sh[2][256];
+    __shared__ bool last;
+    const double N = exp2(logn);
+    const int64_t j0 = (int64_t)blockIdx.x * per;
+    const uint64_t low = (1ull << nloc) - 1;
+    double v[2] = {0.0, 0.0};
+    for (int64_t i = threadIdx.x; i < per && j0 + i < count; i += 256) {
+        const int64_t j = j0 + i;
+        const uint64_t ph = apply_runs(bits[j], l2p);
+        double2 s = {0.0, 0.0};
+        if (tcols == nullptr) {
+            const auto a = psi[ph];
+            s.x = (double)a.x;
+            s.y = (double)a.y;
+        } else {
+            const int r = rowmap[ph >> nloc];
+            for (int t = 0; t < ns; ++t) {
+                const auto a = psi[((uint64_t)t << nloc) | (ph & low)];
+                const double2 w = tcols[(int64_t)t * ns + r];
+                const double ar = (double)a.x, ai = (double)a.y;
+                s.x += w.x * ar - w.y * ai;
+                s.y += w.x * ai + w.y * ar;
+            }
+        }
+        out[j] = s;
+        if (stats) {
+            const double p = N * (s.x * s.x + s.y * s.y);
+            v[0] += p;
+            v[1] += log(p);
+        }
+    }
+    if (!stats) return;
+    double* mine = part + ((int)kPartDoubles - kReducePart);
+    block_tree<2>(sh, v);
+    if (threadIdx.x == 0) {
+        mine[2 * blockIdx.x] = v[0];
+        mine[2 * blockIdx.x + 1] = v[1];
+        __threadfence();
+        last = atomicAdd(ticket, 1u) == gridDim.x - 1;
+    }
+    __syncthreads();
+    if (!last) return;
+    __threadfence();
+    v[0] = v[1] = 0.0;
+    for (int b = threadIdx.x; b < (int)gridDim.x; b += 256) {
+        v[0] += mine[2 * b];
+        v[1] += mine[2 * b + 1];
+    }
+    block_tree<2>(sh, v);
+    double w[1] = {0.0};
+    for (int b = threadIdx.x; b < norm_count; b += 256) w[0] += part[b];
+    __syncthreads();
+    block_tree<1>(*(double(*)[1][256])sh, w);
+    if (threadIdx.x == 0) {
+        stats[0] = w[0];
+        stats[1] = v[0];
+        stats[2] = v[1];
+        *ticket = 0;
+    }
+}
+
+hipError_t launch_reduce(hipStream_t st, const void* psi, int dtype, int nloc, int ns, const BitRuns& log_to_phys,
+                         int64_t count, const uint64_t* bits, const void* tcols, const int* rowmap, double* out,
+                         double logn, double* part, int norm_count, unsigned* ticket, double* stats)
+{
+    if (count < 1 && !stats) return hipSuccess;
+    if (norm_count > (int)kPartDoubles - kReducePart) return hipErrorInvalidValue;
+    const RunsK r = to_k(log_to_phys);
+    int64_t nb = (count + 255) / 256;
+    if (nb < 1) nb = 1;
+    if (nb > kReduceBlocks) nb = kReduceBlocks;
+    const int64_t per = (count + nb - 1) / nb;
+    if (dtype == 0)
+        hipLaunchKernelGGL(k_reduce<float>, dim3((unsigned)nb), dim3(256), 0, st, (const float2*)psi, nloc, ns, r, count,
+                           per, bits, (const double2*)tcols, rowmap, (double2*)out, logn, part, norm_count, ticket,
+                           stats);
+    else
+        hipLaunchKernelGGL(k_reduce<double>, dim3((unsigned)nb), dim3(256), 0, st, (const double2*)psi, nloc, ns, r,
+                           count, per, bits, (const double2*)tcols, rowmap, (double2*)out, logn, part, norm_count,
+                           ticket, stats);
+    return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
+// small uploads
+// ---------------------------------------------------------------------------
+struct UploadK {
+    uint4 d[kUploadMax / 16];
+};
+
+__global__ __launch_bounds__(256) void k_upload(uint4* __restrict__ dst, int n16, UploadK u)
+{
+    if ((int)threadIdx.x < n16) dst[threadIdx.x] = u.d[threadIdx.x];
+}
+
+hipError_t launch_upload(hipStream_t st, void* dst, const void* src, size_t bytes)
+{
+    static_assert(kUploadMax % 16 == 0 && kUploadMax / 16 <= 256, "one access a lane");
+    if (bytes > kUploadMax || bytes % 16) return hipErrorInvalidValue;
+    UploadK u;
+    std::memcpy(u.d, src, bytes);
+    hipLaunchKernelGGL(k_upload, dim3(1), dim3(256), 0, st, (uint4*)dst, (int)(bytes / 16), u);
     return hipGetLastError();
 }
 

@@ -55,11 +55,10 @@ struct WorkBufs {
     void* part;          // kPartDoubles FP64 partial sums
     void* tcol;          // T columns (ns * ns complex128) + ns FP64 slice norms
     void* rowmap;        // ns int
-    void* small;         // 8 doubles
+    void* small;         // 8 doubles: results, and from byte kTicketAt on k_reduce's ticket (zero)
     void* arena;         // queued matrices / tables
     size_t arena_cap;
 };
-constexpr size_t kPartDoubles = 4096 * 2;
 
 // The reduction behind reduce_slices with its work buffers taken from wb
 // (nullptr: the handle's own, allocated on demand).
@@ -126,7 +125,11 @@ struct sv_state {
     void* d_part = nullptr;  size_t d_part_cap = 0;
     void* d_tcol = nullptr;  size_t d_tcol_cap = 0;
     void* d_rowmap = nullptr; size_t d_rowmap_cap = 0;
-    void* d_small = nullptr;              // 8 doubles
+    void* d_small = nullptr;              // 8 doubles (as WorkBufs::small)
+    bool ticket_ready = false;            // d_small's ticket was zeroed (by the first reduction)
+    // pinned staging of a resident reduction: 64 bytes of sums, the
+    // bitstrings, the amplitudes
+    void* h_red = nullptr;   size_t h_red_cap = 0;
 
     // options and accounting
     bool timing = false, fold = true;

@@ -407,6 +407,68 @@ def test_sweep_profile_splits_kinds():
 
 
 @pytest.mark.parametrize("dtype", ["c64", "c128"])
+@pytest.mark.parametrize("count", [0, 1, 255, 257, (1 << 17), (1 << 17) + 1, 600_000])
+def test_reduce_counts(count, dtype):
+    """The one-launch reduction: no bitstrings, one workgroup, several, the
+    largest call through pinned memory and the first one past it, more
+    bitstrings than workgroups times lanes; two calls in a row.  Amplitudes
+    are read exactly; the FP64 sums of at most 600,000 terms agree with
+    numpy's within 1e-12."""
+    n = 16
+    rng = np.random.default_rng(count + 3)
+    psi = W.random_state(n, rng).astype(np.complex64 if dtype == "c64" else np.complex128)
+    h, t = state_from_numpy(psi, dtype)
+    try:
+        for rep in range(2):
+            bits = W.bitstrings(n, count, seed=count + rep) if count else np.zeros(0, dtype=np.uint64)
+            amps, stats = sv.reduce_slices(h, bits)
+            ref = psi[bits.astype(np.int64)].astype(np.complex128)
+            assert np.array_equal(amps, ref)
+            p = 2.0 ** n * np.abs(ref) ** 2
+            want = (np.sum(np.abs(psi.astype(np.complex128)) ** 2), np.sum(p), np.sum(np.log(p)))
+            assert np.allclose(stats, want, rtol=1e-12, atol=1e-9), (stats, want)
+            assert np.array_equal(sv.gather_amplitudes(h, bits), ref)
+    finally:
+        sv.destroy_state(h)
+
+
+@pytest.mark.parametrize("dtype", ["c64", "c128"])
+def test_reduce_resident_slices_with_trailing(dtype):
+    """A resident state with sliced qubits: the sum over all slices in one
+    launch, with and without a trailing operator, after a permute that
+    changes the sliced set."""
+    n, S = 13, (2, 7, 11)
+    rng = np.random.default_rng(5)
+    st = sv.State(n, sum(1 << q for q in S), dtype)
+    try:
+        psi = orc.zero_state(n)
+        for q in range(n):
+            if q not in S:
+                u = W.random_unitary(2, rng)
+                st.fused([q], u)
+                orc.apply_dense(psi, [q], u)
+        order = st.order()
+        order[0], order[n - 1] = order[n - 1], order[0]
+        st.permute(order)
+        for q in order[:n - 3]:
+            u = W.random_unitary(2, rng)
+            st.fused([q], u)
+            orc.apply_dense(psi, [q], u)
+        sliced = sorted(order[n - 3:])
+        T = rng.standard_normal((8, 8)) + 1j * rng.standard_normal((8, 8))
+        bits = np.arange(1 << n, dtype=np.uint64)
+        for trailing in (None, T):
+            got, stats = st.reduce(bits, trailing)
+            ref = psi.copy()
+            if trailing is not None:
+                orc.apply_dense(ref, sliced, trailing)
+            assert orc.rel_l2(got, ref) <= TOL[dtype] * 0.1
+            assert abs(stats[0] - 1.0) <= (1e-5 if dtype == "c64" else 1e-12)
+    finally:
+        st.close()
+
+
+@pytest.mark.parametrize("dtype", ["c64", "c128"])
 @pytest.mark.parametrize("n,sliced", [(1, 0), (2, 0), (7, 0), (8, 0), (9, 0), (10, 0), (14, 0), (14, 3), (11, 3)])
 def test_diag_positions(n, sliced, dtype):
     """A diagonal gate on its own: positions inside an access (0), inside a
