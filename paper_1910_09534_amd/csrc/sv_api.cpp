@@ -485,28 +485,39 @@ bool injected_io_failure(sv_state* h)
             return fail_dev((h), "host-tier transfer (injected failure)", hipErrorUnknown, SV_EIO); \
     } while (0)
 
-int stage_in(sv_state* h, hipStream_t st, uint64_t t, void* slot)
+// The files of one slice between the pinned tier and a device slot.  The tier
+// is one allocation and switching the sliced set relabels its files by moving
+// index bits, so a slice's files lie at one stride from one another, or at a
+// few: each such run is one two-dimensional copy (hipMemcpy2DAsync takes
+// pitches below 2 GiB).  A pass over all slices, both directions at once, with
+// a copy per file -> per run: 2^24 amplitudes in files of 512 KiB 7.4 -> 3.9 ms,
+// 2^28 in files of 512 KiB 171 -> 57, 2 MiB 97 -> 49, 8 MiB 82 -> 47 ms (46 GB/s
+// each way).
+int stage_files(sv_state* h, hipStream_t st, uint64_t t, void* slot, bool in)
 {
-    const size_t fa = file_amps(h), fb = fa * h->amp;
+    const size_t fb = file_amps(h) * h->amp;
     const int nf = 1 << h->s;
-    for (int u = 0; u < nf; ++u) {
-        char* dst = (char*)slot + (size_t)u * fb;
-        CHECK_INJECTED_IO(h);
-        TRY_IO(h, hipMemcpyAsync(dst, h->files[t * nf + u], fb, hipMemcpyHostToDevice, st));
-        h->counters[4] += (int64_t)fb;
-    }
-    return SV_OK;
-}
-
-int stage_out(sv_state* h, hipStream_t st, uint64_t t, const void* slot)
-{
-    const size_t fa = file_amps(h), fb = fa * h->amp;
-    const int nf = 1 << h->s;
-    for (int u = 0; u < nf; ++u) {
-        const char* src = (const char*)slot + (size_t)u * fb;
-        CHECK_INJECTED_IO(h);
-        TRY_IO(h, hipMemcpyAsync(h->files[t * nf + u], src, fb, hipMemcpyDeviceToHost, st));
-        h->counters[5] += (int64_t)fb;
+    void* const* f = &h->files[t * nf];
+    for (int u = 0; u < nf;) {
+        int run = 1;
+        ptrdiff_t pitch = (ptrdiff_t)fb;
+        if (u + 1 < nf) {
+            const ptrdiff_t d = (char*)f[u + 1] - (char*)f[u];
+            if (d >= (ptrdiff_t)fb && d < ((ptrdiff_t)1 << 31)) {
+                pitch = d;
+                while (u + run < nf && (char*)f[u + run] - (char*)f[u + run - 1] == d) ++run;
+            }
+        }
+        for (int i = 0; i < run; ++i) CHECK_INJECTED_IO(h);
+        char* dev = (char*)slot + (size_t)u * fb;
+        if (run == 1 || pitch == (ptrdiff_t)fb)
+            TRY_IO(h, in ? hipMemcpyAsync(dev, f[u], fb * run, hipMemcpyHostToDevice, st)
+                         : hipMemcpyAsync(f[u], dev, fb * run, hipMemcpyDeviceToHost, st));
+        else
+            TRY_IO(h, in ? hipMemcpy2DAsync(dev, fb, f[u], (size_t)pitch, fb, run, hipMemcpyHostToDevice, st)
+                         : hipMemcpy2DAsync(f[u], (size_t)pitch, dev, fb, fb, run, hipMemcpyDeviceToHost, st));
+        h->counters[in ? 4 : 5] += (int64_t)fb * run;
+        u += run;
     }
     return SV_OK;
 }
@@ -530,7 +541,7 @@ int tier_pass_pinned(sv_state* h, bool write_back, F&& visit)
         void* slot = h->slots[k];
         if (idx >= R) TRY(h, hipStreamWaitEvent(h->s_in, h->ev_out[k], 0));
         if (idx >= R) TRY(h, hipStreamWaitEvent(h->s_in, h->ev_comp[k], 0));
-        int rc = stage_in(h, h->s_in, (uint64_t)t, slot);
+        int rc = stage_files(h, h->s_in, (uint64_t)t, slot, true);
         if (rc) return rc;
         TRY(h, hipEventRecord(h->ev_in[k], h->s_in));
         TRY(h, hipStreamWaitEvent(h->stream, h->ev_in[k], 0));
@@ -550,7 +561,7 @@ int tier_pass_pinned(sv_state* h, bool write_back, F&& visit)
         TRY(h, hipEventRecord(h->ev_comp[k], h->stream));
         if (write_back) {
             TRY(h, hipStreamWaitEvent(h->s_out, h->ev_comp[k], 0));
-            rc = stage_out(h, h->s_out, (uint64_t)t, slot);
+            rc = stage_files(h, h->s_out, (uint64_t)t, slot, false);
             if (rc) return rc;
         }
         TRY(h, hipEventRecord(h->ev_out[k], h->s_out));
@@ -920,11 +931,10 @@ void release(sv_state* h)
     if (h->own_dev && h->dev) (void)hipFree(h->dev);
     if (h->scratch) (void)hipFree(h->scratch);
     const size_t fbytes = h->files.empty() ? 0 : ((size_t)1 << (h->L - h->s)) * h->famp;
-    for (void* p : h->files) {
-        if (!p) continue;
-        if (h->pinned_tier) (void)hipHostFree(p);
-        else munmap(p, fbytes);
-    }
+    if (h->slab) (void)hipHostFree(h->slab);
+    else
+        for (void* p : h->files)
+            if (p) munmap(p, fbytes);
     for (int fd : h->file_fds) (void)close(fd);
     if (!h->keep_files) {
         for (const auto& path : h->file_paths) (void)unlink(path.c_str());
@@ -1032,20 +1042,14 @@ int create_common(int n, uint64_t slice_mask, int dtype, void* stream, void* ext
         h->pinned_tier = (fb * h->files.size() <= kPinnedBudget) && !(dtype & SV_FLAG_PAGEABLE) && !dir &&
                          !h->store32;
         if (h->pinned_tier) {
-            for (auto& f : h->files) {
-                if (hipHostMalloc(&f, fb, hipHostMallocDefault) != hipSuccess) {
-                    f = nullptr;
-                    (void)hipGetLastError();
-                    h->pinned_tier = false;
-                    break;
-                }
-                std::memset(f, 0, fb);
+            if (hipHostMalloc(&h->slab, fb * h->files.size(), hipHostMallocDefault) != hipSuccess) {
+                h->slab = nullptr;
+                (void)hipGetLastError();
+                h->pinned_tier = false;
+            } else {
+                for (size_t i = 0; i < h->files.size(); ++i) h->files[i] = (char*)h->slab + i * fb;
+                std::memset(h->slab, 0, fb * h->files.size());
             }
-            if (!h->pinned_tier)
-                for (auto& f : h->files) {
-                    if (f) (void)hipHostFree(f);
-                    f = nullptr;
-                }
         }
         if (dir) {
             // one file per logical file (Sec. 4: slices go to secondary storage
@@ -1786,6 +1790,17 @@ int sv_reset(sv_handle h)
     TRY(h, hipStreamSynchronize(h->s_in));
     TRY(h, hipStreamSynchronize(h->s_out));
     const size_t fb = file_amps(h) * h->famp;
+    if (h->pinned_tier && fb % 16 == 0) {
+        // cleared by the device over the host link
+        const double one[2] = {1.0, 0.0};
+        const float onef[4] = {1.0f, 0.0f, 0.0f, 0.0f};
+        TRY(h, launch_init(h->s_in, h->slab, 1, fb * h->files.size() / 16, false));
+        TRY(h, launch_upload(h->s_in, h->files[0], h->famp == 16 ? (const void*)one : (const void*)onef, 16));
+        TRY(h, hipStreamSynchronize(h->s_in));
+        std::fill(h->slice_zero.begin(), h->slice_zero.end(), (uint8_t)1);
+        h->slice_zero[0] = 0;
+        return SV_OK;
+    }
     for (size_t i = 0; i < h->files.size(); ++i) {
         void* f = h->files[i];
         if (h->pinned_tier) {

@@ -95,7 +95,8 @@ struct sv_state {
 
     // host tier
     std::vector<void*> files;             // [t * 2^s + u], 2^(L-s) amplitudes each
-    bool pinned_tier = true;              // files pinned (hipHostMalloc) or pageable (mmap)
+    bool pinned_tier = true;              // files pinned (parts of one allocation) or pageable (mmap)
+    void* slab = nullptr;                 // the pinned allocation
     bool store32 = false;                 // complex128 state whose files hold complex64
     int famp = 8;                         // bytes per amplitude in the files
     std::vector<int> file_fds;            // file-backed tier: one open file per logical file

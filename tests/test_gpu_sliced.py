@@ -287,3 +287,37 @@ def test_checkpoint_refused_outside_files():
         assert e.value.code == sv.SV_EINVAL
     finally:
         st.close()
+
+
+@pytest.mark.parametrize("n,S,dtype", [(8, (0, 2, 5, 7), "c64"), (8, (0, 2, 5, 7), "c128"), (12, (5,), "c128"),
+                                       (13, (0, 6, 12), "c64"), (14, (2, 3, 9, 11), "c128"), (21, (4,), "c128")])
+def test_pinned_tier_runs_of_files(n, S, dtype):
+    """The files of a slice move in runs of one stride: contiguous, strided
+    and mixed runs after re-layouts of the sliced set, files of one
+    amplitude up to 8 MiB, and a reset in between whose zeros later slices
+    read.  The tier against a resident state: a hundred gates of a few
+    roundings each stay far below the tolerances."""
+    _gpu()
+    rng = np.random.default_rng(n)
+    mask = sum(1 << q for q in S)
+    sts = [sv.State(n, mask, dtype, tier=t) for t in (True, False)]
+    cdt = np.complex64 if dtype == "c64" else np.complex128
+    idx = np.arange(1 << n, dtype=np.uint64)
+    try:
+        for rnd in range(5):
+            order = [int(x) for x in rng.permutation(n)]
+            gates = [W.random_unitary(2, rng).astype(cdt) for _ in range(n)]
+            got = []
+            for st in sts:
+                if rnd == 2:
+                    sv.reset(st.h)
+                st.permute(order)
+                sliced = set(order[n - len(S):])
+                for q in range(n):
+                    if q not in sliced:
+                        st.fused([q], gates[q])
+                got.append(st.gather(idx))
+            assert orc.rel_l2(got[0], got[1]) <= TOL[dtype]
+    finally:
+        for st in sts:
+            st.close()
