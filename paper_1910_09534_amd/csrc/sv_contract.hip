@@ -9,19 +9,25 @@
 // out (M x N) = t2^T (M x K) * t1 (K x N): dense, bound by the matrix
 // cores once K reaches a few tens.
 //
-//   k_contract_mfma   complex64, M >= 128, N >= 64, K >= 16: 128 x 64 output
-//                     tiles per 256-lane workgroup, 64 x 32 per wave, as
-//                     three real products per 16 x 16 block (3M form:
-//                     P1 = Br Ar, P2 = Bi Ai, P3 = (Br + Bi)(Ar + Ai);
-//                     re = P1 - P2, im = P3 - P1 - P2) on v_mfma_f32_16x16x4f32,
-//                     K in chunks of 16 through double-buffered LDS, the next
-//                     chunk's global loads in flight during the products.
-//   k_contract_full   complex128, and complex64 below those sizes, from 16 x 16
+//   k_contract_split  complex64, large products: the split-fp16 form, 128 x 128
+//                     or 128 x 64 output tiles.
+//   k_contract_mfma   the same on the fp32 matrix cores where the caller asks
+//                     for it: 128 x 64 output tiles per 256-lane workgroup,
+//                     64 x 32 per wave, as three real products per 16 x 16
+//                     block (3M form: P1 = Br Ar, P2 = Bi Ai,
+//                     P3 = (Br + Bi)(Ar + Ai); re = P1 - P2,
+//                     im = P3 - P1 - P2) on v_mfma_f32_16x16x4f32, K in chunks
+//                     of 16 through double-buffered LDS, the next chunk's
+//                     global loads in flight during the products.
+//   k_contract_full   complex128, and small complex64 products, from 16 x 16
 //                     outputs and K = 4: four real products in the data's own
 //                     precision.
 //   k_contract_plain  what is left (an output side below 16, K below 4): one
 //                     output per lane, a loop over K.
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <type_traits>
 
 #include "sv_device.h"
 
@@ -29,6 +35,7 @@ namespace sv {
 
 namespace {
 
+typedef float f2v __attribute__((ext_vector_type(2)));
 typedef float f4v __attribute__((ext_vector_type(4)));
 
 constexpr int kCM = 128;          // output rows (x2) per workgroup
@@ -168,8 +175,8 @@ __global__ __launch_bounds__(kCThreads) void k_contract_mfma(const float2* t1, c
 }
 
 // ---- split-fp16 form of the matrix-core contraction -----------------------
-// The same 128 x 64 output tiles and 16-deep K chunks, with the products on
-// the fp16 matrix cores at single-precision accuracy: every input is scaled
+// 16-deep K chunks as above, with the products on the fp16 matrix cores at
+// single-precision accuracy: every input is scaled
 // by a power of two (from the largest |component| of its tensor, so that it
 // stays below 2^14) and split into hi = f16(x) and lo = f16(x - hi); the
 // three products A_hi B_hi + A_hi B_lo + A_lo B_hi accumulate in fp32 on
@@ -180,6 +187,16 @@ __global__ __launch_bounds__(kCThreads) void k_contract_mfma(const float2* t1, c
 // is parked in LDS already split, each row's 16 values contiguous (hi and
 // lo of the real and imaginary parts), so a lane reads its 8 operand
 // values with one 16-byte access.
+// A wave's tile is 64 x 16 CB.  With 64 x 32 (CB = 2) the LDS is busy for 0.92
+// of the time that the products take (16 reads and 12 values split per 48
+// products), with 64 x 64 (CB = 4: 24 and 16 per 96) for 0.67; that needs 234
+// of the 256 registers that two waves per SIMD have.  The next chunk is split
+// and parked in four pieces between the products of this one, and each
+// piece's registers are loaded again for the chunk after it.  13, 15, 8: 1,690
+// us in 64 x 32 with the split after the products, 1,600 in 64 x 64, 1,567 as
+// it is (1.05 PFLOP/s of the 24 MNK issued; the vendor's fp16 product reaches
+// 1.38), the clock down to 1.7 GHz under the load; 15, 15, 10: 25.3 -> 23.6 ->
+// 22.7 ms (1.16).
 typedef _Float16 ch8 __attribute__((ext_vector_type(8)));
 typedef _Float16 ch4 __attribute__((ext_vector_type(4)));
 typedef uint32_t cu4 __attribute__((ext_vector_type(4)));
@@ -195,24 +212,34 @@ __device__ __forceinline__ int srow(int r, int o)
     return r * kSRow + ((o ^ ((r >> 2) & 1)) << 3);
 }
 
-// largest |component| of count floats, as float bits, into *out (atomic
-// max: non-negative floats order as their bit patterns)
-__global__ __launch_bounds__(256) void k_absmax(const float* __restrict__ x, uint64_t count, uint32_t* out)
+// largest |component| of t2 (blocks below `split`) and of t1 (the others), as
+// float bits, into out[0] and out[1] (atomic max: non-negative floats order as
+// their bit patterns); four 16-byte loads in flight per lane
+__global__ __launch_bounds__(256) void k_absmax(const float4* __restrict__ t2, uint64_t count2,
+                                                const float4* __restrict__ t1, uint64_t count1, uint32_t split,
+                                                uint32_t* out)
 {
-    __shared__ float sh[256];
+    __shared__ float sh[4];
+    const bool first = blockIdx.x < split;
+    const float4* x = first ? t2 : t1;
+    const uint64_t count = first ? count2 : count1;
+    const uint64_t stride = (uint64_t)(first ? split : gridDim.x - split) * 256;
+    uint64_t i = (uint64_t)(first ? blockIdx.x : blockIdx.x - split) * 256 + threadIdx.x;
     float m = 0.f;
-    const uint64_t stride = (uint64_t)gridDim.x * 256 * 4;
-    for (uint64_t i = ((uint64_t)blockIdx.x * 256 + threadIdx.x) * 4; i < count; i += stride) {
-        const float4 v = *(const float4*)(x + i);
-        m = fmaxf(m, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
+    auto take = [&](float4 v) { m = fmaxf(m, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w)))); };
+    for (; i + 3 * stride < count; i += 4 * stride) {
+        const float4 v0 = x[i], v1 = x[i + stride], v2 = x[i + 2 * stride], v3 = x[i + 3 * stride];
+        take(v0);
+        take(v1);
+        take(v2);
+        take(v3);
     }
-    sh[threadIdx.x] = m;
+    for (; i < count; i += stride) take(x[i]);
+#pragma unroll
+    for (int h = 32; h > 0; h >>= 1) m = fmaxf(m, __shfl_xor(m, h));
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = m;
     __syncthreads();
-    for (int h = 128; h > 0; h >>= 1) {
-        if ((int)threadIdx.x < h) sh[threadIdx.x] = fmaxf(sh[threadIdx.x], sh[threadIdx.x + h]);
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) atomicMax(out, __float_as_uint(sh[0]));
+    if (threadIdx.x == 0) atomicMax(out + (first ? 0 : 1), __float_as_uint(fmaxf(fmaxf(sh[0], sh[1]), fmaxf(sh[2], sh[3]))));
 }
 
 // exponent s with max 2^s <= 2^14 (0 for an all-zero tensor)
@@ -225,83 +252,87 @@ __device__ __forceinline__ int scale_exp(uint32_t maxbits)
     return e < -100 ? -100 : (e > 100 ? 100 : e);
 }
 
-__global__ __launch_bounds__(kCThreads) void k_contract_split(const float2* t1, const float2* t2,
-                                                              float2* __restrict__ out, int n1, int n2, int e,
-                                                              uint32_t tiles_n, uint32_t group,
-                                                              const uint32_t* __restrict__ maxbits)
+template <int CB>
+__global__ __launch_bounds__(kCThreads, CB == 4 ? 2 : 3) void k_contract_split(const float2* t1, const float2* t2,
+                                                                 float2* __restrict__ out, int n1, int n2, int e,
+                                                                 uint32_t tiles_n, uint32_t group,
+                                                                 const uint32_t* __restrict__ maxbits, bool nt)
 {
+    constexpr int CN = 32 * CB;                // output columns per workgroup
+    constexpr int NK = CB == 4 ? 8 : 4;        // k values of a t1 column a lane stages
     // [buffer][part: re hi, re lo, im hi, im lo][row][k]
     __shared__ __attribute__((aligned(16))) _Float16 Bs[2][4][kCM * kSRow];
-    __shared__ __attribute__((aligned(16))) _Float16 As[2][4][kCN * kSRow];
+    __shared__ __attribute__((aligned(16))) _Float16 As[2][4][CN * kSRow];
     const uint64_t N = 1ull << n1, M = 1ull << n2;
     const uint32_t K = 1u << e;
     const uint32_t per = group * tiles_n;
     const uint32_t gq = blockIdx.x / per, rr = blockIdx.x % per;
     const uint32_t tn = rr / group, tm = gq * group + rr % group;
-    const uint64_t m0 = (uint64_t)tm * kCM, n0 = (uint64_t)tn * kCN;
+    const uint64_t m0 = (uint64_t)tm * kCM, n0 = (uint64_t)tn * CN;
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63;
-    const int wm = (wave >> 1) * 64, wn = (wave & 1) * 32;
+    const int wm = (wave >> 1) * 64, wn = (wave & 1) * 16 * CB;
     const int li = lane & 15, g = lane >> 4;
+    // staging: t2 column m = tid % 128, k = 8 (tid / 128) + 0..7; t1 column
+    // n = tid % CN, k = NK (tid / CN) + 0..NK-1 (each load row is 64 lanes of
+    // consecutive columns)
+    const int bm = tid & 127, bo = tid >> 7;
+    const int an = tid & (CN - 1), aq = tid / CN;
+    const uint32_t nchunks = K / kCK;
+    float2 gb[8], ga[NK];
+    auto load_b = [&](uint32_t c) {
+        const float2* pb = t2 + (uint64_t)(c * kCK + 8 * bo) * M + m0 + bm;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) gb[k] = pb[(uint64_t)k * M];
+    };
+    auto load_a = [&](uint32_t c) {
+        const float2* pa = t1 + (uint64_t)(c * kCK + NK * aq) * N + n0 + an;
+#pragma unroll
+        for (int k = 0; k < NK; ++k) ga[k] = pa[(uint64_t)k * N];
+    };
+    load_b(0);
+    load_a(0);
+    __builtin_amdgcn_sched_barrier(0);
     const int eb = scale_exp(maxbits[0]), ea = scale_exp(maxbits[1]);
     // (the two factors are applied one after the other on the way out:
     // 2^-(eb + ea) alone can leave the float range)
     const float sb = ldexpf(1.f, eb), sa = ldexpf(1.f, ea), ub = ldexpf(1.f, -eb), ua = ldexpf(1.f, -ea);
 
-    // staging: t2 column m = tid % 128, k = 8 (tid / 128) + 0..7; t1 column
-    // n = tid % 64, k = 4 (tid / 64) + 0..3 (each load row is 64 lanes of
-    // consecutive columns)
-    const int bm = tid & 127, bo = tid >> 7;
-    const int an = tid & 63, aq = tid >> 6;
-    const uint32_t nchunks = K / kCK;
-    float2 gb[8], ga[4];
-    auto load = [&](uint32_t c) {
-        const float2* pb = t2 + (uint64_t)(c * kCK + 8 * bo) * M + m0 + bm;
-        const float2* pa = t1 + (uint64_t)(c * kCK + 4 * aq) * N + n0 + an;
+    // piece 0, 1: real and imaginary parts of the staged t2 values; 2, 3: of t1
+    using au = typename std::conditional<CB == 4, cu4, cu2>::type;
+    const int pob = srow(bm, bo);
+    const int poa = CB == 4 ? srow(an, aq) : srow(an, aq >> 1) + 4 * (aq & 1);
+    auto park = [&](int buf, int piece) {
+        const bool im = piece & 1;
+        if (piece < 2) {
+            cu4 hi, lo;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) gb[k] = pb[(uint64_t)k * M];
+            for (int w = 0; w < 4; ++w) {
+                const float x0 = im ? gb[2 * w].y : gb[2 * w].x, x1 = im ? gb[2 * w + 1].y : gb[2 * w + 1].x;
+                hi[w] = cpk_hi(x0, x1, sb);
+                lo[w] = cpk_lo(x0, x1, sb, hi[w]);
+            }
+            *(cu4*)&Bs[buf][2 * im][pob] = hi;
+            *(cu4*)&Bs[buf][2 * im + 1][pob] = lo;
+        } else {
+            au hi, lo;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) ga[k] = pa[(uint64_t)k * N];
-    };
-    auto park = [&](int buf) {
-        cu4 rh, rl, ih, il;
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            const float x0 = gb[2 * w].x, x1 = gb[2 * w + 1].x;
-            const float y0 = gb[2 * w].y, y1 = gb[2 * w + 1].y;
-            rh[w] = cpk_hi(x0, x1, sb);
-            ih[w] = cpk_hi(y0, y1, sb);
-            rl[w] = cpk_lo(x0, x1, sb, rh[w]);
-            il[w] = cpk_lo(y0, y1, sb, ih[w]);
+            for (int w = 0; w < NK / 2; ++w) {
+                const float x0 = im ? ga[2 * w].y : ga[2 * w].x, x1 = im ? ga[2 * w + 1].y : ga[2 * w + 1].x;
+                hi[w] = cpk_hi(x0, x1, sa);
+                lo[w] = cpk_lo(x0, x1, sa, hi[w]);
+            }
+            *(au*)&As[buf][2 * im][poa] = hi;
+            *(au*)&As[buf][2 * im + 1][poa] = lo;
         }
-        const int ob = srow(bm, bo);
-        *(cu4*)&Bs[buf][0][ob] = rh;
-        *(cu4*)&Bs[buf][1][ob] = rl;
-        *(cu4*)&Bs[buf][2][ob] = ih;
-        *(cu4*)&Bs[buf][3][ob] = il;
-        cu2 arh, arl, aih, ail;
-#pragma unroll
-        for (int w = 0; w < 2; ++w) {
-            const float x0 = ga[2 * w].x, x1 = ga[2 * w + 1].x;
-            const float y0 = ga[2 * w].y, y1 = ga[2 * w + 1].y;
-            arh[w] = cpk_hi(x0, x1, sa);
-            aih[w] = cpk_hi(y0, y1, sa);
-            arl[w] = cpk_lo(x0, x1, sa, arh[w]);
-            ail[w] = cpk_lo(y0, y1, sa, aih[w]);
-        }
-        const int oa = srow(an, aq >> 1) + 4 * (aq & 1);
-        *(cu2*)&As[buf][0][oa] = arh;
-        *(cu2*)&As[buf][1][oa] = arl;
-        *(cu2*)&As[buf][2][oa] = aih;
-        *(cu2*)&As[buf][3][oa] = ail;
     };
 
-    f4v re[4][2], im[4][2];
+    f4v re[4][CB], im[4][CB];
 #pragma unroll
     for (int a = 0; a < 4; ++a)
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
+        for (int b = 0; b < CB; ++b) {
             re[a][b] = f4v{0.f, 0.f, 0.f, 0.f};
             im[a][b] = re[a][b];
         }
@@ -309,60 +340,77 @@ __global__ __launch_bounds__(kCThreads) void k_contract_split(const float2* t1, 
     // (g < 2) or the imaginary part (g >= 2).  Re = [Br | Bi] [Ar ; -Ai] and
     // Im = [Br | Bi] [Ai ; Ar]: both products share the A operand, and the
     // -Ai of the real one is the sign flipped in lanes g >= 2 of its other
-    // operand (two 16-column blocks per wave, against four 16-row blocks
-    // of the A operand)
+    // operand
     const int o = g & 1;
     const int pA = g < 2 ? 0 : 2;                 // A operand rows: Br or Bi
     const int pBr = g < 2 ? 0 : 2;                // [Ar ; Ai], Ai negated below
     const int pBi = g < 2 ? 2 : 0;                // [Ai ; Ar]
     const uint32_t neg = g < 2 ? 0u : 0x80008000u;
 
-    load(0);
-    park(0);
-    __syncthreads();
-    for (uint32_t c = 0; c < nchunks; ++c) {
-        const int buf = c & 1;
-        if (c + 1 < nchunks) load(c + 1);
-        __builtin_amdgcn_sched_barrier(0);
-        ch8 xbr_h[2], xbr_l[2], xbi_h[2], xbi_l[2];
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            const int ob = srow(wn + 16 * b + li, o);
-            xbr_h[b] = __builtin_bit_cast(ch8, *(const cu4*)&As[buf][pBr][ob] ^ neg);
-            xbr_l[b] = __builtin_bit_cast(ch8, *(const cu4*)&As[buf][pBr + 1][ob] ^ neg);
-            xbi_h[b] = *(const ch8*)&As[buf][pBi][ob];
-            xbi_l[b] = *(const ch8*)&As[buf][pBi + 1][ob];
-        }
+    auto chunk = [&](int buf, auto more, uint32_t next) {
+        ch8 ah[4], al[4];
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
             const int oa = srow(wm + 16 * a + li, o);
-            const cu4 h = *(const cu4*)&Bs[buf][pA][oa];
-            const cu4 l = *(const cu4*)&Bs[buf][pA + 1][oa];
-            const ch8 a_h = __builtin_bit_cast(ch8, h), a_l = __builtin_bit_cast(ch8, l);
+            ah[a] = *(const ch8*)&Bs[buf][pA][oa];
+            al[a] = *(const ch8*)&Bs[buf][pA + 1][oa];
+        }
 #pragma unroll
-            for (int b = 0; b < 2; ++b) {
-                re[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a_l, xbr_h[b], re[a][b], 0, 0, 0);
-                im[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a_l, xbi_h[b], im[a][b], 0, 0, 0);
-                re[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a_h, xbr_l[b], re[a][b], 0, 0, 0);
-                im[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a_h, xbi_l[b], im[a][b], 0, 0, 0);
-                re[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a_h, xbr_h[b], re[a][b], 0, 0, 0);
-                im[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a_h, xbi_h[b], im[a][b], 0, 0, 0);
+        for (int b = 0; b < CB; ++b) {
+            const int ob = srow(wn + 16 * b + li, o);
+            const ch8 rh = __builtin_bit_cast(ch8, *(const cu4*)&As[buf][pBr][ob] ^ neg);
+            const ch8 rl = __builtin_bit_cast(ch8, *(const cu4*)&As[buf][pBr + 1][ob] ^ neg);
+            const ch8 ih = *(const ch8*)&As[buf][pBi][ob];
+            const ch8 il = *(const ch8*)&As[buf][pBi + 1][ob];
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                re[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al[a], rh, re[a][b], 0, 0, 0);
+                im[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al[a], ih, im[a][b], 0, 0, 0);
+            }
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                re[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[a], rl, re[a][b], 0, 0, 0);
+                im[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[a], il, im[a][b], 0, 0, 0);
+            }
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                re[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[a], rh, re[a][b], 0, 0, 0);
+                im[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[a], ih, im[a][b], 0, 0, 0);
+            }
+            if (more) {
+#pragma unroll
+                for (int p = b * 4 / CB; p < (b + 1) * 4 / CB; ++p) {
+                    park(buf ^ 1, p);
+                    if (p == 1) load_b(next);
+                    if (p == 3) load_a(next);
+                }
             }
         }
-        __builtin_amdgcn_sched_barrier(0);
-        if (c + 1 < nchunks) park(buf ^ 1);
+    };
+#pragma unroll
+    for (int p = 0; p < 4; ++p) park(0, p);
+    const uint32_t last = nchunks - 1;
+    load_b(last ? 1 : 0);
+    load_a(last ? 1 : 0);
+    __syncthreads();
+    uint32_t c = 0;
+    for (; c < last; ++c) {
+        chunk(c & 1, std::true_type{}, c + 2 < last ? c + 2 : last);
         __syncthreads();
     }
+    chunk(c & 1, std::false_type{}, 0);
     // lane holds rows 4 g + v of each 16-row block, column li of each 16-column block
 #pragma unroll
     for (int a = 0; a < 4; ++a)
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+        for (int b = 0; b < CB; ++b)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const uint64_t m = m0 + wm + 16 * a + 4 * g + v;
                 const uint64_t n = n0 + wn + 16 * b + li;
-                out[m * N + n] = float2{re[a][b][v] * ub * ua, im[a][b][v] * ub * ua};
+                const float2 r = float2{re[a][b][v] * ub * ua, im[a][b][v] * ub * ua};
+                if (nt) __builtin_nontemporal_store(f2v{r.x, r.y}, (f2v*)(out + m * N + n));
+                else out[m * N + n] = r;
             }
 }
 
@@ -409,7 +457,6 @@ __global__ __launch_bounds__(SK > 1 ? 64 * SK : 256) void k_contract_full(
     using F = Full<T>;
     using V = typename F::V;
     using acc = typename F::acc;
-    static_assert(SK == 1 || (RB == 1 && CB == 1), "the parts of a sum are added block by block");
     const uint64_t N = 1ull << n1, M = 1ull << n2;
     const uint32_t steps = (1u << (e - 2)) / SK;         // four k each
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -471,22 +518,25 @@ __global__ __launch_bounds__(SK > 1 ? 64 * SK : 256) void k_contract_full(
     if constexpr (SK > 1) {
         // item c = 2 v + {re, im} of lane l, one row of SK parts: lane l's
         // items are added by threads l + 64 c (all of them in flight at once)
-        __shared__ T part[SK][8 * 64];
+        __shared__ T part[SK][RB * CB * 8 * 64];
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            part[wave][64 * (2 * v) + lane] = rr[0][0][v] - ii[0][0][v];
-            part[wave][64 * (2 * v + 1) + lane] = ri[0][0][v] + ir[0][0][v];
-        }
+        for (int q = 0; q < RB * CB; ++q)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int a = q / CB, b = q % CB;
+                part[wave][64 * (8 * q + 2 * v) + lane] = rr[a][b][v] - ii[a][b][v];
+                part[wave][64 * (8 * q + 2 * v + 1) + lane] = ri[a][b][v] + ir[a][b][v];
+            }
         __syncthreads();
-        for (int i = threadIdx.x; i < 4 * 64; i += 64 * SK) {
-            const int l = i & 63, v = i >> 6;
+        for (int i = threadIdx.x; i < RB * CB * 4 * 64; i += 64 * SK) {
+            const int l = i & 63, v = (i >> 6) & 3, q = i >> 8;
             T sr = 0, si = 0;
 #pragma unroll
             for (int w = 0; w < SK; ++w) {
-                sr += part[w][64 * (2 * v) + l];
-                si += part[w][64 * (2 * v + 1) + l];
+                sr += part[w][64 * (8 * q + 2 * v) + l];
+                si += part[w][64 * (8 * q + 2 * v + 1) + l];
             }
-            out[(m0 + F::row(l >> 4, v)) * N + n0 + (l & 15)] = V{sr, si};
+            out[(m0 + 16 * (q / CB) + F::row(l >> 4, v)) * N + n0 + 16 * (q % CB) + (l & 15)] = V{sr, si};
         }
         return;
     }
@@ -514,7 +564,9 @@ hipError_t launch_full_tiles(hipStream_t st, const void* t1, const void* t2, voi
 }
 
 // At least 16 x 16 outputs and four k.  32 x 32 outputs a wave where that
-// gives every SIMD one (1,024); 16 x 16 below, with the sum in 16 or 4 parts
+// gives every SIMD one (1,024); in fp32 with the sum in four parts up to 2^22
+// outputs (a quarter of the chain: 9, 9, 8 22.9 us in one part of 16 x 16, 22.0
+// here; error 2.9e-7 and 1.5e-7); 16 x 16 below, with the sum in 16 or 4 parts
 // while the outputs alone leave SIMDs idle and it is long enough to give each
 // wave four steps (2^18 outputs, e = 8: 20.6 us in one part, 22.7 in 16).
 // Measured (n1, n2, e; k_contract_plain -> here): complex128 12, 13, 6
@@ -528,6 +580,8 @@ hipError_t launch_full_tiles(hipStream_t st, const void* t1, const void* t2, voi
 template <typename T>
 hipError_t launch_full(hipStream_t st, const void* t1, const void* t2, void* out, int n1, int n2, int e)
 {
+    if (std::is_same<T, float>::value && n2 >= 5 && n1 >= 5 && n1 + n2 >= 18 && n1 + n2 <= 22 && e >= 5)
+        return launch_full_tiles<float, 2, 2, 1, 4>(st, t1, t2, out, n1, n2, e);
     if (n2 >= 5 && n1 >= 5 && n1 + n2 >= 20) return launch_full_tiles<T, 2, 2, 1, 1>(st, t1, t2, out, n1, n2, e);
     if (n1 + n2 <= 16 && e >= 8) return launch_full_tiles<T, 1, 1, 4, 16>(st, t1, t2, out, n1, n2, e);
     if (n1 + n2 <= 17 && e >= 6) return launch_full_tiles<T, 1, 1, 4, 4>(st, t1, t2, out, n1, n2, e);
@@ -557,15 +611,27 @@ __global__ __launch_bounds__(256) void k_contract_plain(const T* __restrict__ t1
 
 }  // namespace
 
-bool contract_uses_mfma(int dtype, int n1, int n2, int e)
+// complex64 from one 128 x 64 tile and one chunk on, except small products.
+// There the tiles leave CUs idle (2^20 outputs are 128 of them), and the split
+// form takes three more launches than one kernel, so k_contract_full in fp32 is
+// faster up to here, and its error, summed in more parts, no larger.  Measured
+// as calls (n1, n2, e; split / 3M -> full): 8, 8, 8 50 / 47 -> 19 us, 9, 9, 10
+// 98 / 134 -> 39, 10, 10, 6 47 / 26 -> 24, 10, 10, 9 69 / 77 -> 59, 11, 11, 4 48
+// / 25 -> 27, 11, 11, 6 48 / 34 -> 43; past the limits 10, 10, 10 105 / -> 102,
+// 11, 11, 7 54 / 46 -> 63, 12, 12, 4 52 / -> 56.  Relative error against 64
+// bits: 8, 8, 8 2.6e-7 / 4.1e-7 -> 1.1e-7, 10, 10, 9 3.6e-7 / 5.7e-7 -> 2.1e-7,
+// 10, 10, 4 8.8e-8 / 1.2e-7 -> 7.9e-8.
+static bool contract_uses_tiles(int n1, int n2, int e, bool split)
 {
-    return dtype == 0 && n2 >= 7 && n1 >= 6 && e >= 4;
+    if (n2 < 7 || n1 < 6 || e < 4) return false;
+    const int n = n1 + n2;
+    return !(n <= 20 && n + e <= 29) && !(split && n <= 22 && n + e <= 28);
 }
 
 hipError_t launch_contract(hipStream_t st, const void* t1, const void* t2, void* out, int n1, int n2, int e,
                            int dtype, bool split)
 {
-    if (contract_uses_mfma(dtype, n1, n2, e)) {
+    if (dtype == 0 && contract_uses_tiles(n1, n2, e, split)) {
         const uint64_t tiles = (1ull << (n2 - 7)) * (1ull << (n1 - 6));
         if (tiles > 0x7fffffffull) return hipErrorInvalidValue;
         const uint32_t tiles_m = 1u << (n2 - 7);
@@ -574,20 +640,29 @@ hipError_t launch_contract(hipStream_t st, const void* t1, const void* t2, void*
             // the two tensors' largest |component|, in stream-ordered memory
             // (concurrent contractions on other streams keep their own)
             uint32_t* mx = nullptr;
-            hipError_t err = hipMallocAsync((void**)&mx, 2 * sizeof(uint32_t), st);
+            hipError_t err = hipMallocAsync((void**)&mx, 2 * sizeof(uint64_t), st);
             if (err != hipSuccess) return err;
-            err = hipMemsetAsync(mx, 0, 2 * sizeof(uint32_t), st);
+            err = launch_init(st, mx, 1, 1, false);
             if (err != hipSuccess) return err;
-            const uint64_t c2 = 2ull << (n2 + e), c1 = 2ull << (n1 + e);
-            auto grid_for = [](uint64_t count) {
-                uint64_t gsz = (count / 4 + 255) / 256;
-                return (unsigned)(gsz > 2048 ? 2048 : (gsz < 1 ? 1 : gsz));
-            };
-            hipLaunchKernelGGL(k_absmax, dim3(grid_for(c2)), dim3(256), 0, st, (const float*)t2, c2, mx);
-            hipLaunchKernelGGL(k_absmax, dim3(grid_for(c1)), dim3(256), 0, st, (const float*)t1, c1, mx + 1);
-            hipLaunchKernelGGL(k_contract_split, dim3((unsigned)tiles), dim3(kCThreads), 0, st, (const float2*)t1,
-                               (const float2*)t2, (float2*)out, n1, n2, e, (uint32_t)(1ull << (n1 - 6)), group,
-                               (const uint32_t*)mx);
+            const uint64_t c2 = 1ull << (n2 + e - 1), c1 = 1ull << (n1 + e - 1);     // in 16 bytes
+            auto grid_for = [](uint64_t count) { return (uint32_t)std::min<uint64_t>(1024, (count + 1023) / 1024); };
+            const uint32_t g2 = grid_for(c2), g1 = grid_for(c1);
+            hipLaunchKernelGGL(k_absmax, dim3(g2 + g1), dim3(256), 0, st, (const float4*)t2, c2, (const float4*)t1,
+                               c1, g2, mx);
+            // 128 x 128 outputs from two workgroups per CU on (n1, n2, e; 128 x 64
+            // -> 128 x 128: 10, 10, 8 42 -> 47 us, 11, 11, 10 160 -> 158, 12, 13, 8
+            // 247 -> 221, 15, 15, 10 25.8 -> 23.0 ms); non-temporal stores where
+            // the outputs exceed the 256 MB cache (plain -> non-temporal: 12, 13,
+            // 4 64 -> 75 us, 13, 14, 9 1,505 -> 1,471, 13, 15, 8 1,614 -> 1,567)
+            const bool nt = n1 + n2 >= 26;
+            if (n1 >= 7 && n1 + n2 >= 23)
+                hipLaunchKernelGGL((k_contract_split<4>), dim3((unsigned)(tiles / 2)), dim3(kCThreads), 0, st,
+                                   (const float2*)t1, (const float2*)t2, (float2*)out, n1, n2, e,
+                                   (uint32_t)(1ull << (n1 - 7)), group, (const uint32_t*)mx, nt);
+            else
+                hipLaunchKernelGGL((k_contract_split<2>), dim3((unsigned)tiles), dim3(kCThreads), 0, st,
+                                   (const float2*)t1, (const float2*)t2, (float2*)out, n1, n2, e,
+                                   (uint32_t)(1ull << (n1 - 6)), group, (const uint32_t*)mx, nt);
             err = hipGetLastError();
             const hipError_t e2 = hipFreeAsync(mx, st);
             return err != hipSuccess ? err : e2;

@@ -161,7 +161,6 @@ uint64_t stage_visits(int nloc, int nops, const int* ks, const int* const* pos, 
 
 // Contraction over entanglement indices: out[x2 2^n1 + x1] =
 // sum_e t1[e 2^n1 + x1] t2[e 2^n2 + x2] (complex64 or complex128).
-bool contract_uses_mfma(int dtype, int n1, int n2, int e);
 hipError_t launch_contract(hipStream_t st, const void* t1, const void* t2, void* out, int n1, int n2, int e,
                            int dtype, bool split = true);
 

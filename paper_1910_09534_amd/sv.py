@@ -316,8 +316,8 @@ def contract(t1_ptr: int, t2_ptr: int, out_ptr: int, n1: int, n2: int, e: int, d
              fp32: bool = False) -> None:
     """out[x2 2^n1 + x1] = sum_c t1[c 2^n1 + x1] t2[c 2^n2 + x2] on device
     buffers (see sv_contract in include/sv.h).  Asynchronous on `stream`.
-    fp32: complex64 products in the 3M form on the fp32 matrix cores instead
-    of the split-fp16 form."""
+    fp32: large complex64 products in the 3M form on the fp32 matrix cores
+    instead of the split-fp16 form."""
     code = _dtype_code(dtype) | (SV_CONTRACT_FP32 if fp32 else 0)
     _check(lib().sv_contract(t1_ptr, t2_ptr, out_ptr, n1, n2, e, code, stream))
 

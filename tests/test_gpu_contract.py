@@ -79,6 +79,34 @@ def test_contract_full_precision_tiles(n1, n2, e, dtype):
     assert orc.rel_l2(got, ref) <= bound, orc.rel_l2(got, ref)
 
 
+@pytest.mark.parametrize("n1,n2,e,fp32,scale", [
+    (6, 7, 5, False, 1), (9, 9, 5, False, 1), (10, 10, 9, True, 1), (11, 11, 6, False, 1), (15, 5, 6, False, 1),
+    (11, 11, 4, True, 1), (11, 11, 7, False, 1), (6, 15, 8, False, 1e10), (9, 10, 11, False, 1e-12),
+    (7, 16, 4, False, 1), (13, 10, 5, False, 1e10), (16, 7, 6, False, 1e-12), (12, 14, 4, False, 1),
+    (6, 20, 4, False, 1)])
+def test_contract_tile_choice(n1, n2, e, fp32, scale):
+    """Complex64 on both sides of each line of the tile choice: fp32 with the
+    sum in one, 4 and 16 parts, the 3M form, split-fp16 tiles of 128 x 64 and
+    128 x 128 outputs with one, two and more chunks, plain and non-temporal
+    stores.  16 columns x2 are checked in full.  sqrt(K) eps for the sums with
+    a factor 4 for the complex product's real sums, as above, and another 2
+    for the 3M form's cancellations; the split adds at most 2^-21."""
+    torch = _torch()
+    rng = np.random.default_rng(n1 * 1000 + n2 * 10 + e + 11)
+    t1 = (_rand((1 << e) << n1, rng) * scale).astype(np.complex64)
+    t2 = _rand((1 << e) << n2, rng).astype(np.complex64)
+    g1, g2 = torch.from_numpy(t1).cuda(), torch.from_numpy(t2).cuda()
+    out = torch.full((1 << (n1 + n2),), complex(7.0, 7.0), dtype=g1.dtype, device="cuda")
+    sv.contract(g1.data_ptr(), g2.data_ptr(), out.data_ptr(), n1, n2, e, "c64",
+                torch.cuda.current_stream().cuda_stream, fp32=fp32)
+    torch.cuda.synchronize()
+    rows = np.unique(np.concatenate([[0, (1 << n2) - 1], rng.integers(0, 1 << n2, 14)]))
+    got = out.view(1 << n2, 1 << n1)[torch.from_numpy(rows).cuda()].cpu().numpy()
+    ref = t2.reshape(1 << e, 1 << n2)[:, rows].T.astype(np.complex128) @ t1.reshape(1 << e, 1 << n1)
+    assert orc.rel_l2(got.astype(np.complex128).ravel(), ref.ravel()) <= 8 * 2.0 ** -24 * np.sqrt(1 << e) + 2.0 ** -21
+    assert np.abs(got - ref).max() <= 1e-5 * np.sqrt(1 << e) * scale
+
+
 @pytest.mark.parametrize("s1,s2", [(1e-6, 1.0), (1.0, 3e5), (1e-15, 1e-12), (1e10, 1e-10)])
 def test_contract_split_accuracy_independent_of_scale(s1, s2):
     """The split-fp16 form scales each tensor from its own largest component:
