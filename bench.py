@@ -79,7 +79,7 @@ FP64_PEAK_TFLOPS = 78.6            # FP64 (vector and matrix cores)
 
 KERNEL_SOURCES = ("paper_1910_09534_amd/csrc/sv_device.h", "paper_1910_09534_amd/csrc/sv_kernels.hip",
                   "paper_1910_09534_amd/csrc/sv_mfma.hip", "paper_1910_09534_amd/csrc/sv_stage.hip",
-                  "paper_1910_09534_amd/csrc/sv_split.hip",
+                  "paper_1910_09534_amd/csrc/sv_split.hip", "paper_1910_09534_amd/csrc/sv_stage64.hip",
                   "paper_1910_09534_amd/csrc/sv_internal.h")
 TRAFFIC_FILE = "profiles/staged_pass_30q_d14_traffic.json"
 BATCH_TUNED = "profiles/batch_256_circuits_tuned.json"

@@ -281,7 +281,7 @@ enum {
                               to the widest width the LDS holds for its blocks'
                               matrices; in the split-fp16 form 14 measured fastest
                               for states of 2^23 to 2^30 amplitudes, in the fp32 form
-                              13 at 2^30; complex128: one 512-lane workgroup per CU, tiles
+                              13 at 2^30; complex128: eight waves per CU, tiles
                               of at most 13 positions, products on the FP64 matrix
                               cores); 0: one pass per block; other values: SV_EINVAL */
     SV_OPT_FAIL_IO = 6,    /* failure injection for tests: the n-th host-tier transfer

@@ -120,12 +120,12 @@ inline bool dense_uses_mfma(int k, int nloc, int mfma_min_k)
 // taken as zero instead of read.  *tile_mask_out: the tile's positions;
 // *amps_out: amplitudes visited.
 // dtype 0: complex64 (fp32 or split-fp16 form); 1: complex128 (FP64 form,
-// one 512-lane workgroup per CU, tiles of 9..13 positions).
+// eight waves per CU, tiles of 9..13 positions).
 int stage_lds_bytes(int t, int nops, const int* ks, int dtype = 0);
 // LDS budget of a tile of t positions (complex64: 80 KiB up to 13, two
 // workgroups per CU; 160 KiB at 14, one workgroup per CU; complex128:
-// 160 KiB).  The sizes are those of the fp32 form's padded tiles; the split
-// form's take no more.
+// 160 KiB).  The sizes are those of padded tiles, as the fp32 form has them;
+// the other two forms' take no more.
 int stage_lds_limit(int t, int dtype = 0);
 // Sets the staged kernels' LDS attribute for every tile width (idempotent;
 // launch_stage does it on first use, graph capture needs it beforehand).
@@ -149,6 +149,11 @@ hipError_t launch_split(hipStream_t st, void* psi, int t, const int* P, int nops
                         const int* const* pos, const void* const* mats, uint64_t tiles, uint64_t tmask,
                         uint64_t newmask, bool from_e0, double* norm_out, int* norm_blocks, int split_exp);
 hipError_t split_prepare(int t, int lds);
+// The same for complex128 (sv_stage64.hip).
+hipError_t launch_stage64(hipStream_t st, void* psi, int t, const int* P, int nops, const int* ks,
+                          const int* const* pos, const void* const* mats, uint64_t tiles, uint64_t tmask,
+                          uint64_t newmask, bool from_e0, double* norm_out, int* norm_blocks);
+hipError_t stage64_prepare(int lds);
 // Exponent e of the split-fp16 form's tile scale 2^e for a run whose
 // blocks are all unitary and whose state norm stays below bound: the
 // largest e with 2^e bound <= 2^15 (-100..100); kNoSplit when bound is not

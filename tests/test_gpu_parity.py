@@ -809,3 +809,37 @@ def test_c128_staged_circuit_from_reset(n):
     finally:
         st.close()
     assert cnt["staged_blocks"] >= 4, cnt
+
+
+@pytest.mark.parametrize("start", ["dense", "reset"])
+@pytest.mark.parametrize("t", [9, 10, 11, 12, 13])
+def test_c128_staged_block_forms(t, start):
+    """4- and 5-qubit blocks as the only, first, middle and last block of an
+    FP64 staged pass, on low, high and mixed targets, on every tile width, on
+    a dense state and from a reset (tiles with unreached positions), the
+    pass's norm included.  A block sums 32 products in each of three real
+    products whose terms cancel by a factor of 3 at most: 2^-53 sqrt(32) 3,
+    2e-15, with a factor 2.5 to spare: 5e-15 a block."""
+    n = t + 5
+    rng = np.random.default_rng(1300 + t)
+    for ks in [(4,), (5,), (4, 5), (5, 4), (5, 5), (4, 4, 4), (5, 4, 5), (4, 5, 4), (4, 4, 5, 4)]:
+        pool = [0, 1, 2, 3] + [int(x) for x in rng.choice(np.arange(4, n), size=5, replace=False)]
+        psi = W.random_state(n, rng)
+        h, tensor = state_from_numpy(psi, "c128")
+        try:
+            sv.set_option(h, sv.SV_OPT_STAGE, t)
+            if start == "reset":
+                sv.reset(h)
+                psi = orc.zero_state(n)
+            ref = psi.astype(np.complex128).copy()
+            for k in ks:
+                qs = [int(x) for x in rng.choice(pool, size=k, replace=False)]
+                u = W.random_unitary(1 << k, rng)
+                sv.apply_fused(h, qs, u, "c128")
+                orc.apply_dense(ref, qs, u)
+            got, stats = sv.reduce_slices(h, np.arange(1 << n, dtype=np.uint64))
+            assert sv.counters(h)["staged_blocks"] >= 1
+            assert orc.rel_l2(got, ref) <= 5e-15 * len(ks), (t, ks)
+            assert abs(stats[0] - orc.norm(ref)) <= 1e-14 * len(ks)
+        finally:
+            sv.destroy_state(h)
