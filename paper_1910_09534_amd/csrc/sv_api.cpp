@@ -414,7 +414,17 @@ int run_ops(sv_state* h, hipStream_t st, void** psi, void* alt, int nloc, uint64
             h->counters[1] += 1;
             h->counters[3] += (int64_t)1 << nloc;
         } else {
-            TRY(h, launch_bitperm(st, *psi, alt, h->dtype, nloc, op.runs));
+            BitRuns r = op.runs;
+            if (nloc > h->L) {
+                // slices side by side: the sliced positions stay
+                const uint64_t top = (((uint64_t)1 << nloc) - 1) & ~(((uint64_t)1 << h->L) - 1);
+                int i = 0;
+                while (i < r.count && r.shift[i] != 0) ++i;
+                if (i == kMaxRuns) return set_err(h, SV_EINVAL, "internal: too many runs in a local permute");
+                r.mask[i] |= top;
+                r.count = std::max(r.count, i + 1);
+            }
+            TRY(h, launch_bitperm(st, *psi, alt, h->dtype, nloc, r));
             std::swap(*psi, alt);
             h->counters[2] += 1;
             h->counters[3] += (int64_t)1 << nloc;
@@ -522,6 +532,89 @@ int stage_files(sv_state* h, hipStream_t st, uint64_t t, void* slot, bool in)
     return SV_OK;
 }
 
+// Where the 2^nbits files from `first` on lie, as offsets of the file index's
+// bits (switching the sliced set moves bits of it); false when they do not lie
+// like that.
+bool file_bits(const sv_state* h, uint64_t first, int nbits, FilesK& a)
+{
+    const size_t fb = file_amps(h) * h->amp;
+    if (nbits > kMaxFileBits || fb % 16 || (fb & (fb - 1))) return false;
+    char* const* f = (char* const*)&h->files[first];
+    a.host = f[0];
+    a.s = nbits;
+    a.lg = 0;
+    while (((size_t)16 << a.lg) < fb) ++a.lg;
+    for (int b = 0; b < nbits; ++b) a.off[b] = f[1ull << b] - f[0];
+    for (uint64_t u = 1; u < 1ull << nbits; ++u)
+        if (f[u] != f[u & (u - 1)] + a.off[__builtin_ctzll(u)]) return false;
+    return true;
+}
+
+int stage_kernel(sv_state* h, void* dev, const FilesK& a, uint64_t slices, bool in)
+{
+    for (uint64_t u = 0; u < slices << h->s; ++u) CHECK_INJECTED_IO(h);
+    TRY_IO(h, launch_files(h->stream, dev, a, in));
+    h->counters[in ? 4 : 5] += (int64_t)(slices * ((file_amps(h) * h->amp) << h->s));
+    return SV_OK;
+}
+
+// A small pinned tier: every slice on the device at once, one pass over all of
+// them (slices are the state's top positions), one launch in and one out.  A
+// slice of its own costs 35 us of launches, or 100 us of copies and events; the
+// pipeline of slices overlaps both directions of the link and pays from there.
+// 12 layers on 16 slices, reset to amplitudes, copies a slice -> kernels a slice
+// -> at once: 16 qubits complex64 4.3 -> 2.1 -> 0.8 ms, 20 qubits (8 MiB) 5.0 ->
+// 4.0 -> 2.3, complex128 (16 MiB) 5.5 -> 6.1 -> 3.8, 23 qubits complex64 (64 MiB)
+// 11.4 -> 15.5 -> 12.3.
+constexpr size_t kWholeTier = (size_t)16 << 20;
+
+template <class F>
+int tier_pass_whole(sv_state* h, bool write_back, F&& visit, bool& taken)
+{
+    const int ns = 1 << h->s;
+    const size_t slice = (file_amps(h) * h->amp) << h->s;
+    std::vector<FilesK> files(ns);
+    FilesK all{};
+    int zeros = 0;
+    for (int t = 0; t < ns; ++t) zeros += h->slice_zero[t] != 0;
+    if (zeros == 0) {
+        if (!(taken = file_bits(h, 0, 2 * h->s, all))) return SV_OK;
+    } else {
+        for (int t = 0; t < ns; ++t)
+            if (!h->slice_zero[t] && !(taken = file_bits(h, (uint64_t)t << h->s, h->s, files[t]))) return SV_OK;
+    }
+    // (no memory for it: slice by slice)
+    taken = ensure_dev(h, &h->d_whole, &h->d_whole_cap, slice * ns) == SV_OK &&
+            ensure_dev(h, &h->d_whole2, &h->d_whole2_cap, slice * ns) == SV_OK;
+    if (!taken) return h->poisoned ? SV_EDEVICE : SV_OK;
+    int rc;
+    h->counters[6] += zeros;
+    void* cur = h->d_whole;
+    auto move = [&](bool in) {
+        if (zeros == 0) return stage_kernel(h, cur, all, ns, in);
+        for (int t = 0; t < ns; ++t) {
+            if (h->slice_zero[t]) continue;
+            const int r = stage_kernel(h, (char*)cur + t * slice, files[t], 1, in);
+            if (r) return r;
+        }
+        return (int)SV_OK;
+    };
+    if (zeros) TRY(h, launch_init(h->stream, cur, 1, slice * ns / 16, false));
+    if ((rc = move(true))) return rc;
+    if ((rc = run_ops(h, h->stream, &cur, h->d_whole2, h->n, 0))) return rc;
+    for (int t = 0; t < ns; ++t)
+        if (!h->slice_zero[t] && (rc = visit(t, (char*)cur + t * slice))) return rc;
+    if (write_back && (rc = move(false))) return rc;
+    TRY(h, hipStreamSynchronize(h->stream));
+    return SV_OK;
+}
+
+// Files up to this size move by kernels that read and write the host memory:
+// a row of a two-dimensional copy costs about 2 us, and a kernel's copy runs in
+// one direction at a time (a pass over 2^27 amplitudes in slices of 128 files
+// of 64 KiB: 64 -> 44 ms; 2^25 in 32 of 256 KiB: 8.7 -> 11.0).
+constexpr size_t kKernelFile = (size_t)64 << 10;
+
 // Run the queue over every non-zero slice of the tier: stage in (copy-in
 // stream), compute (handle stream), stage out (copy-out stream), pipelined
 // over the device slots.  visit (optional) runs on the compute stream after
@@ -531,10 +624,35 @@ int tier_pass_pinned(sv_state* h, bool write_back, F&& visit)
 {
     const int ns = 1 << h->s;
     const int R = (int)h->slots.size();
+    const size_t fb = file_amps(h) * h->amp;
+    if ((fb << (2 * h->s)) <= kWholeTier) {
+        bool taken = false;
+        const int rc = tier_pass_whole(h, write_back, visit, taken);
+        if (taken || rc) return rc;
+    }
+    const bool small = fb <= kKernelFile;
     int idx = 0;
     for (int t = 0; t < ns; ++t) {
         if (h->slice_zero[t]) {
             h->counters[6] += 1;
+            continue;
+        }
+        FilesK files;
+        if (small && file_bits(h, (uint64_t)t << h->s, h->s, files)) {
+            // copies by kernels, everything in order on the compute stream
+            void* slot = h->slots[0];
+            int rc = stage_kernel(h, slot, files, 1, true);
+            if (rc) return rc;
+            void* cur = slot;
+            rc = run_ops(h, h->stream, &cur, h->pslot, h->L, (uint64_t)t << h->L);
+            if (rc) return rc;
+            if (cur != slot) {
+                h->slots[0] = cur;
+                h->pslot = slot;
+            }
+            rc = visit(t, cur);
+            if (rc) return rc;
+            if (write_back && (rc = stage_kernel(h, cur, files, 1, false))) return rc;
             continue;
         }
         const int k = idx % R;
@@ -929,6 +1047,8 @@ void release(sv_state* h)
     if (h->s_in) (void)hipStreamSynchronize(h->s_in);
     if (h->s_out) (void)hipStreamSynchronize(h->s_out);
     if (h->own_dev && h->dev) (void)hipFree(h->dev);
+    if (h->d_whole) pool_free(h->d_whole, h->d_whole_cap, false);
+    if (h->d_whole2) pool_free(h->d_whole2, h->d_whole2_cap, false);
     if (h->scratch) (void)hipFree(h->scratch);
     const size_t fbytes = h->files.empty() ? 0 : ((size_t)1 << (h->L - h->s)) * h->famp;
     if (h->slab) (void)hipHostFree(h->slab);

@@ -215,6 +215,17 @@ hipError_t launch_reduce(hipStream_t st, const void* psi, int dtype, int nloc, i
 constexpr size_t kUploadMax = 3584;
 hipError_t launch_upload(hipStream_t st, void* dst, const void* src, size_t bytes);
 
+// 2^s files in pinned memory, 16 << lg bytes each: file u lies at host + the
+// offsets of u's set bits.  launch_files copies them to (in) or from a device
+// buffer, where they are contiguous.
+constexpr int kMaxFileBits = 24;
+struct FilesK {
+    void* host;
+    int s, lg;
+    int64_t off[kMaxFileBits];
+};
+hipError_t launch_files(hipStream_t st, void* slot, const FilesK& a, bool in);
+
 // Deterministic FP64 sum of |psi|^2 over 2^nloc amplitudes: writes
 // nblocks partial sums to partial (device), returns the block count used.
 hipError_t launch_norm_partials(hipStream_t st, const void* psi, int dtype, int nloc,

@@ -861,4 +861,31 @@ hipError_t launch_upload(hipStream_t st, void* dst, const void* src, size_t byte
     return hipGetLastError();
 }
 
+// ---------------------------------------------------------------------------
+// a slice of the pinned tier to or from a device slot, over the host link
+// ---------------------------------------------------------------------------
+template <bool IN>
+__global__ __launch_bounds__(256) void k_files(uint4* __restrict__ slot, FilesK a)
+{
+    const uint64_t n16 = 1ull << (a.s + a.lg), stride = (uint64_t)gridDim.x * 256;
+    for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < n16; i += stride) {
+        int64_t at = (int64_t)(i & ((1ull << a.lg) - 1)) * 16;
+        for (int b = 0; b < a.s; ++b)
+            if ((i >> (a.lg + b)) & 1) at += a.off[b];
+        uint4* host = (uint4*)((char*)a.host + at);
+        if (IN) slot[i] = *host;
+        else *host = slot[i];
+    }
+}
+
+hipError_t launch_files(hipStream_t st, void* slot, const FilesK& a, bool in)
+{
+    if (a.s < 0 || a.s > kMaxFileBits || a.lg < 0 || a.s + a.lg > 32) return hipErrorInvalidValue;
+    const uint64_t n16 = 1ull << (a.s + a.lg);
+    const dim3 grid((unsigned)std::min<uint64_t>((n16 + 255) / 256, 1024));
+    if (in) hipLaunchKernelGGL(k_files<true>, grid, dim3(256), 0, st, (uint4*)slot, a);
+    else hipLaunchKernelGGL(k_files<false>, grid, dim3(256), 0, st, (uint4*)slot, a);
+    return hipGetLastError();
+}
+
 }  // namespace sv

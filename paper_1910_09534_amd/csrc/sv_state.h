@@ -97,6 +97,8 @@ struct sv_state {
     std::vector<void*> files;             // [t * 2^s + u], 2^(L-s) amplitudes each
     bool pinned_tier = true;              // files pinned (parts of one allocation) or pageable (mmap)
     void* slab = nullptr;                 // the pinned allocation
+    void *d_whole = nullptr, *d_whole2 = nullptr;   // a small pinned tier's slices, all at once
+    size_t d_whole_cap = 0, d_whole2_cap = 0;
     bool store32 = false;                 // complex128 state whose files hold complex64
     int famp = 8;                         // bytes per amplitude in the files
     std::vector<int> file_fds;            // file-backed tier: one open file per logical file

@@ -290,12 +290,13 @@ def test_checkpoint_refused_outside_files():
 
 
 @pytest.mark.parametrize("n,S,dtype", [(8, (0, 2, 5, 7), "c64"), (8, (0, 2, 5, 7), "c128"), (12, (5,), "c128"),
-                                       (13, (0, 6, 12), "c64"), (14, (2, 3, 9, 11), "c128"), (21, (4,), "c128")])
+                                       (13, (0, 6, 12), "c64"), (14, (2, 3, 9, 11), "c128"), (20, (1, 8, 9, 17), "c128"),
+                                       (21, (4,), "c128"), (22, (0, 3, 7, 12, 20), "c64")])
 def test_pinned_tier_runs_of_files(n, S, dtype):
     """The files of a slice move in runs of one stride: contiguous, strided
     and mixed runs after re-layouts of the sliced set, files of one
     amplitude up to 8 MiB, and a reset in between whose zeros later slices
-    read.  The tier against a resident state: a hundred gates of a few
+    read; tiers up to 16 MiB as a whole, and 22 qubits with files of 32 KiB.  The tier against a resident state: a hundred gates of a few
     roundings each stay far below the tolerances."""
     _gpu()
     rng = np.random.default_rng(n)
