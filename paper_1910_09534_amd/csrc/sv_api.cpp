@@ -495,6 +495,33 @@ bool injected_io_failure(sv_state* h)
             return fail_dev((h), "host-tier transfer (injected failure)", hipErrorUnknown, SV_EIO); \
     } while (0)
 
+// Files up to this size move by kernels that read and write the host memory:
+// a row of a two-dimensional copy costs about 2 us, and a kernel's copy runs in
+// one direction at a time (a pass over 2^27 amplitudes in slices of 128 files
+// of 64 KiB: 64 -> 44 ms; 2^25 in 32 of 256 KiB: 8.7 -> 11.0).
+constexpr size_t kKernelFile = (size_t)64 << 10;
+
+// Pinned tiers up to this size are run as a whole (tier_pass_whole).
+constexpr size_t kWholeTier = (size_t)16 << 20;
+
+// Whether slices go through the three-stream pipeline of copies.
+bool tier_copies(const sv_state* h)
+{
+    const size_t fb = file_amps(h) * h->amp;
+    return fb > kKernelFile && (fb << (2 * h->s)) > kWholeTier;
+}
+
+// All files of a fresh state but those of slice 0 hold zeros: where slices move
+// by copies they are only marked, and a slice that a switch of the sliced set
+// has put together from them reads the others alone (24 qubits in 16 slices, 12
+// layers, reset to amplitudes: 22.1 -> 20.2 ms, 25 qubits 30.5 -> 25.1).
+void mark_zero_files(sv_state* h)
+{
+    const bool lazy = tier_copies(h);
+    h->file_zero.assign(h->files.size(), 0);
+    if (lazy) std::fill(h->file_zero.begin() + (1 << h->s), h->file_zero.end(), (uint8_t)1);
+}
+
 // The files of one slice between the pinned tier and a device slot.  The tier
 // is one allocation and switching the sliced set relabels its files by moving
 // index bits, so a slice's files lie at one stride from one another, or at a
@@ -508,14 +535,27 @@ int stage_files(sv_state* h, hipStream_t st, uint64_t t, void* slot, bool in)
     const size_t fb = file_amps(h) * h->amp;
     const int nf = 1 << h->s;
     void* const* f = &h->files[t * nf];
+    uint8_t* zero = &h->file_zero[t * nf];
+    if (in) {
+        // files that hold zeros are cleared in the slot instead of read
+        bool any = false;
+        for (int u = 0; u < nf; ++u) any = any || zero[u];
+        if (any) TRY_IO(h, launch_init(st, slot, 1, fb * nf / 16, false));
+    } else {
+        std::fill(zero, zero + nf, (uint8_t)0);
+    }
     for (int u = 0; u < nf;) {
+        if (zero[u]) {
+            ++u;
+            continue;
+        }
         int run = 1;
         ptrdiff_t pitch = (ptrdiff_t)fb;
-        if (u + 1 < nf) {
+        if (u + 1 < nf && !zero[u + 1]) {
             const ptrdiff_t d = (char*)f[u + 1] - (char*)f[u];
             if (d >= (ptrdiff_t)fb && d < ((ptrdiff_t)1 << 31)) {
                 pitch = d;
-                while (u + run < nf && (char*)f[u + run] - (char*)f[u + run - 1] == d) ++run;
+                while (u + run < nf && !zero[u + run] && (char*)f[u + run] - (char*)f[u + run - 1] == d) ++run;
             }
         }
         for (int i = 0; i < run; ++i) CHECK_INJECTED_IO(h);
@@ -565,9 +605,7 @@ int stage_kernel(sv_state* h, void* dev, const FilesK& a, uint64_t slices, bool 
 // 12 layers on 16 slices, reset to amplitudes, copies a slice -> kernels a slice
 // -> at once: 16 qubits complex64 4.3 -> 2.1 -> 0.8 ms, 20 qubits (8 MiB) 5.0 ->
 // 4.0 -> 2.3, complex128 (16 MiB) 5.5 -> 6.1 -> 3.8, 23 qubits complex64 (64 MiB)
-// 11.4 -> 15.5 -> 12.3.
-constexpr size_t kWholeTier = (size_t)16 << 20;
-
+// 10.3 -> 15.5 -> 12.3.
 template <class F>
 int tier_pass_whole(sv_state* h, bool write_back, F&& visit, bool& taken)
 {
@@ -609,12 +647,6 @@ int tier_pass_whole(sv_state* h, bool write_back, F&& visit, bool& taken)
     return SV_OK;
 }
 
-// Files up to this size move by kernels that read and write the host memory:
-// a row of a two-dimensional copy costs about 2 us, and a kernel's copy runs in
-// one direction at a time (a pass over 2^27 amplitudes in slices of 128 files
-// of 64 KiB: 64 -> 44 ms; 2^25 in 32 of 256 KiB: 8.7 -> 11.0).
-constexpr size_t kKernelFile = (size_t)64 << 10;
-
 // Run the queue over every non-zero slice of the tier: stage in (copy-in
 // stream), compute (handle stream), stage out (copy-out stream), pipelined
 // over the device slots.  visit (optional) runs on the compute stream after
@@ -624,13 +656,12 @@ int tier_pass_pinned(sv_state* h, bool write_back, F&& visit)
 {
     const int ns = 1 << h->s;
     const int R = (int)h->slots.size();
-    const size_t fb = file_amps(h) * h->amp;
-    if ((fb << (2 * h->s)) <= kWholeTier) {
+    if (((file_amps(h) * h->amp) << (2 * h->s)) <= kWholeTier) {
         bool taken = false;
         const int rc = tier_pass_whole(h, write_back, visit, taken);
         if (taken || rc) return rc;
     }
-    const bool small = fb <= kKernelFile;
+    const bool small = !tier_copies(h);
     int idx = 0;
     for (int t = 0; t < ns; ++t) {
         if (h->slice_zero[t]) {
@@ -1169,6 +1200,7 @@ int create_common(int n, uint64_t slice_mask, int dtype, void* stream, void* ext
             } else {
                 for (size_t i = 0; i < h->files.size(); ++i) h->files[i] = (char*)h->slab + i * fb;
                 std::memset(h->slab, 0, fb * h->files.size());
+                mark_zero_files(h);
             }
         }
         if (dir) {
@@ -1710,6 +1742,7 @@ int permute_qubits(sv_handle h, const int* order)
         // file pointer relabel: old top index (bits at mid positions) -> new top index
         const int ns = 1 << s, nf = 1 << (2 * s);
         std::vector<void*> nfiles(nf, nullptr);
+        std::vector<uint8_t> nfzero(h->file_zero.size());
         std::vector<uint8_t> nzero(ns, 1);
         for (int oldidx = 0; oldidx < nf; ++oldidx) {
             int newidx = 0;
@@ -1717,10 +1750,12 @@ int permute_qubits(sv_handle h, const int* order)
                 if (mid[q] >= F && ((oldidx >> (mid[q] - F)) & 1)) newidx |= 1 << (top_new[q] - F);
             const int ot = oldidx >> s, nt = newidx >> s;
             nfiles[newidx] = h->files[oldidx];
+            if (!nfzero.empty()) nfzero[newidx] = h->file_zero[oldidx];
             if (!h->slice_zero[ot]) nzero[nt] = 0;
         }
         // files of slice t are stored at [t * 2^s + u]: the index above is (t << s) | u
         h->files.swap(nfiles);
+        h->file_zero.swap(nfzero);
         h->slice_zero.swap(nzero);
         // (3) remaining local permutation
         std::vector<int> cur(h->n);
@@ -1911,10 +1946,15 @@ int sv_reset(sv_handle h)
     TRY(h, hipStreamSynchronize(h->s_out));
     const size_t fb = file_amps(h) * h->famp;
     if (h->pinned_tier && fb % 16 == 0) {
-        // cleared by the device over the host link
+        // cleared by the device over the host link: slice 0 where the other
+        // slices' files can be marked, else all of it
+        mark_zero_files(h);
         const double one[2] = {1.0, 0.0};
         const float onef[4] = {1.0f, 0.0f, 0.0f, 0.0f};
-        TRY(h, launch_init(h->s_in, h->slab, 1, fb * h->files.size() / 16, false));
+        if (tier_copies(h))
+            for (int u = 0; u < 1 << h->s; ++u) TRY(h, launch_init(h->s_in, h->files[u], 1, fb / 16, false));
+        else
+            TRY(h, launch_init(h->s_in, h->slab, 1, fb * h->files.size() / 16, false));
         TRY(h, launch_upload(h->s_in, h->files[0], h->famp == 16 ? (const void*)one : (const void*)onef, 16));
         TRY(h, hipStreamSynchronize(h->s_in));
         std::fill(h->slice_zero.begin(), h->slice_zero.end(), (uint8_t)1);

@@ -97,6 +97,7 @@ struct sv_state {
     std::vector<void*> files;             // [t * 2^s + u], 2^(L-s) amplitudes each
     bool pinned_tier = true;              // files pinned (parts of one allocation) or pageable (mmap)
     void* slab = nullptr;                 // the pinned allocation
+    std::vector<uint8_t> file_zero;       // pinned tier, by file: zeros, whatever its memory holds
     void *d_whole = nullptr, *d_whole2 = nullptr;   // a small pinned tier's slices, all at once
     size_t d_whole_cap = 0, d_whole2_cap = 0;
     bool store32 = false;                 // complex128 state whose files hold complex64

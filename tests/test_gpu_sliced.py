@@ -291,7 +291,8 @@ def test_checkpoint_refused_outside_files():
 
 @pytest.mark.parametrize("n,S,dtype", [(8, (0, 2, 5, 7), "c64"), (8, (0, 2, 5, 7), "c128"), (12, (5,), "c128"),
                                        (13, (0, 6, 12), "c64"), (14, (2, 3, 9, 11), "c128"), (20, (1, 8, 9, 17), "c128"),
-                                       (21, (4,), "c128"), (22, (0, 3, 7, 12, 20), "c64")])
+                                       (21, (4,), "c128"), (22, (3, 11), "c64"),
+                                       (22, (0, 3, 7, 12, 20), "c64")])
 def test_pinned_tier_runs_of_files(n, S, dtype):
     """The files of a slice move in runs of one stride: contiguous, strided
     and mixed runs after re-layouts of the sliced set, files of one
