@@ -1,7 +1,7 @@
 // Batch executor: many resident states, their queued operations applied
 // round by round with one launch per (kernel form, k, fold) per round, all
 // rounds optionally captured into one HIP graph (see sv_batch_prepare in
-// include/sv.h: one graph for each of four lanes).
+// include/sv.h: one graph for each lane).
 //
 // Sweep r of every state goes into round r.  Within a round the sweeps of
 // different states touch different buffers, so they share a launch; rounds
@@ -52,9 +52,14 @@ struct Launch {
 // A captured batch runs as kLanes graphs side by side, each on a stream of
 // its own: a state's launches depend on one another only, and a pass over a
 // state of 20 to 23 qubits is mostly latency and leaves most of the chip
-// idle.  The device serves four hardware queues.  Sixteen circuits of 20 to 24
-// qubits take 3.85 ms as four graphs against 5.2 ms as one.
-constexpr int kLanes = 4;
+// idle.  The device serves four hardware queues, and streams share them as the
+// runtime deals them: of four graphs two may meet on one queue, which six
+// balance where the passes fill the time (states from 2^kWideQubits
+// amplitudes), while below that the time is launches and a graph more costs.
+// Sixteen circuits of 20 to 24 qubits take 5.2 ms as one graph, 3.8-4.1 as four,
+// 3.2-3.5 as six, 3.5 as eight; of 20 to 22 qubits 1.5-1.8 as four, 1.7-1.8 as
+// six.  Heaviest lane first: launching the graphs takes 0.4-0.8 ms.
+constexpr int kLanes = 6, kLanesSmall = 4, kWideQubits = 23;
 
 }  // namespace
 
@@ -76,6 +81,7 @@ struct sv_batch_s {
     // writes ahead, staged passes visit only the tiles that can be non-zero
     std::vector<Launch> launches_reset;
     bool captured = false;
+    int lanes = kLanesSmall;
     hipStream_t lane[kLanes] = {};           // [0]: stream
     hipGraph_t graph[2][kLanes] = {};        // [1]: the reset variant
     hipGraphExec_t exec[2][kLanes] = {};
@@ -154,7 +160,7 @@ hipError_t enqueue_all(sv_batch_s* b, const std::vector<Launch>& launches)
 // are dealt out heaviest first, each to the lightest lane.
 std::vector<int> deal_lanes(const sv_batch_s* b)
 {
-    const int count = (int)b->states.size();
+    const int count = (int)b->states.size(), lanes = b->lanes;
     std::vector<int> root(count);
     for (int i = 0; i < count; ++i) root[i] = i;
     auto find = [&](int i) {
@@ -176,7 +182,7 @@ std::vector<int> deal_lanes(const sv_batch_s* b)
     double load[kLanes] = {};
     for (int i : by) {
         if (find(i) != i) continue;
-        const int l = (int)(std::min_element(load, load + kLanes) - load);
+        const int l = (int)(std::min_element(load, load + lanes) - load);
         load[l] += group[i];
         for (int j = 0; j < count; ++j)
             if (find(j) == i) lane[j] = l;
@@ -206,16 +212,16 @@ hipError_t capture_lane(sv_batch_s* b, const std::vector<Launch>& launches, cons
 hipError_t launch_lanes(sv_batch_s* b, const hipGraphExec_t* exec)
 {
     bool fork = false;
-    for (int l = 1; l < kLanes; ++l) fork = fork || exec[l];
+    for (int l = 1; l < b->lanes; ++l) fork = fork || exec[l];
     hipError_t e = hipSuccess;
     if (fork && (e = hipEventRecord(b->ev_fork, b->stream)) != hipSuccess) return e;
-    for (int l = kLanes - 1; l >= 0; --l) {
+    for (int l = 0; l < b->lanes; ++l) {
         if (!exec[l]) continue;
         if (l > 0 && (e = hipStreamWaitEvent(b->lane[l], b->ev_fork, 0)) != hipSuccess) return e;
         if ((e = hipGraphLaunch(exec[l], b->lane[l])) != hipSuccess) return e;
         if (l > 0 && (e = hipEventRecord(b->ev_lane[l], b->lane[l])) != hipSuccess) return e;
     }
-    for (int l = 1; l < kLanes; ++l)
+    for (int l = 1; l < b->lanes; ++l)
         if (exec[l] && (e = hipStreamWaitEvent(b->stream, b->ev_lane[l], 0)) != hipSuccess) return e;
     return e;
 }
@@ -486,15 +492,17 @@ int sv_batch_prepare(int count, sv_handle* handles, int flags, void* hip_stream,
             free_batch(b);
             return berr(nullptr, SV_EDEVICE, "staged kernel set-up failed");
         }
+        for (const sv_state* h : b->states)
+            if (h->n >= kWideQubits) b->lanes = kLanes;
         const std::vector<int> lane = deal_lanes(b);
         b->lane[0] = b->stream;
         e = hipEventCreateWithFlags(&b->ev_fork, hipEventDisableTiming);
-        for (int l = 1; l < kLanes && e == hipSuccess; ++l) {
+        for (int l = 1; l < b->lanes && e == hipSuccess; ++l) {
             e = hipStreamCreateWithFlags(&b->lane[l], hipStreamNonBlocking);
             if (e == hipSuccess) e = hipEventCreateWithFlags(&b->ev_lane[l], hipEventDisableTiming);
         }
         for (int v = 0; v < 2; ++v)
-            for (int l = 0; l < kLanes && e == hipSuccess; ++l)
+            for (int l = 0; l < b->lanes && e == hipSuccess; ++l)
                 e = capture_lane(b, v ? b->launches_reset : b->launches, lane, l, &b->graph[v][l], &b->exec[v][l]);
         b->captured = true;
         if (e != hipSuccess) {
