@@ -366,8 +366,8 @@ int sv_sweep_profile(sv_handle h, double ms[2], int64_t count[2], double flops[2
  * state goes into round r, and each round is one launch per kernel form
  * (matrix-core / VALU), block width k and fold flag, whose workgroups are
  * divided among the states in proportion to their size.  With
- * SV_BATCH_GRAPH all rounds are captured into HIP graphs (one for each of four
- * groups of states that share no launch, replayed side by side), so a batch
+ * SV_BATCH_GRAPH all rounds are captured into HIP graphs (one for each of up to
+ * six groups of states that share no launch, replayed side by side), so a batch
  * can be replayed at the cost of these launches (e.g. after sv_reset of every
  * state).  A second variant (and set of graphs) serves launches where every state was reset
  * since its last use (SV_OPT_SPARSE_START on): staged passes start from

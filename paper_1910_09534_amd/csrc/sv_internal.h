@@ -149,6 +149,8 @@ hipError_t launch_split(hipStream_t st, void* psi, int t, const int* P, int nops
                         const int* const* pos, const void* const* mats, uint64_t tiles, uint64_t tmask,
                         uint64_t newmask, bool from_e0, double* norm_out, int* norm_blocks, int split_exp);
 hipError_t split_prepare(int t, int lds);
+// Tile limit of a pass of one block on 2^bits amplitudes (at most t_max).
+int split_lone_width(int k, const int* pos, int bits, int t_max);
 // The same for complex128 (sv_stage64.hip).
 hipError_t launch_stage64(hipStream_t st, void* psi, int t, const int* P, int nops, const int* ks,
                           const int* const* pos, const void* const* mats, uint64_t tiles, uint64_t tmask,

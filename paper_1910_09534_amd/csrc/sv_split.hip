@@ -52,11 +52,11 @@ namespace sv {
 
 namespace {
 
-constexpr int kSplitMaxOps = 8;
+constexpr int kSplitMaxOps = 8 + 2;   // blocks, and a parking step on either side
 
 struct SplitOp {
     const float2* mat;            // row-major complex matrix (device)
-    int k;
+    int k;                        // 0: a parking step
     int pair;                     // 1: position 0 is a target (canonical bit b0)
     int perm[5];                  // the matrix's own bit of canonical bit b_u
     int image;                    // byte offset of the operand image in LDS
@@ -302,7 +302,7 @@ __global__ __launch_bounds__(split_lanes(TW), 4) void k_split(float2* __restrict
         const SplitOp& op = a.op[o];
         const int k = op.k, D = 1 << k;
         const float2* mat = op.mat;
-        for (int i = threadIdx.x; i < 4 * D; i += NT) {
+        for (int i = threadIdx.x; k && i < 4 * D; i += NT) {
             const int R = i & (D - 1), g = i >> k;
             int row = 0;
 #pragma unroll
@@ -365,6 +365,7 @@ __global__ __launch_bounds__(split_lanes(TW), 4) void k_split(float2* __restrict
             for (int c = 0; c < 4; ++c) nacc = fma((double)y[c], (double)y[c], nacc);
         }
     };
+    using c0 = std::integral_constant<int, 0>;
     using c4 = std::integral_constant<int, 4>;
     using c5 = std::integral_constant<int, 5>;
     auto form = [&](int o, auto&& f) {
@@ -391,7 +392,14 @@ __global__ __launch_bounds__(split_lanes(TW), 4) void k_split(float2* __restrict
             }
         }
         Operands x0;
-        convert<K0, P0, true>(x0, raw, a.scale);
+        if constexpr (K0 == 0) {
+            const float r = a.scale;
+#pragma unroll
+            for (int m = 0; m < 8; ++m) out0(m, f4{raw[m][0] * r, raw[m][1] * r, raw[m][2] * r, raw[m][3] * r});
+            __builtin_amdgcn_sched_barrier(0);
+        } else {
+            convert<K0, P0, true>(x0, raw, a.scale);
+        }
         nb = ((tb | ~a.tmask) + a.tstep) & a.tmask;
         tile += gridDim.x;
         next = tile < a.tiles;
@@ -399,7 +407,7 @@ __global__ __launch_bounds__(split_lanes(TW), 4) void k_split(float2* __restrict
         load_tile(nb, next && !a.from_e0);
         __builtin_amdgcn_s_setprio(0);
         __builtin_amdgcn_sched_barrier(0);
-        apply<K0, P0>(lds, a.op[0].image, lane, x0, out0);
+        if constexpr (K0 != 0) apply<K0, P0>(lds, a.op[0].image, lane, x0, out0);
     };
     // the first tile's loads end here, as every later tile's do at the loop's
     // end: waits inside the loop then never cover the stores
@@ -424,14 +432,22 @@ __global__ __launch_bounds__(split_lanes(TW), 4) void k_split(float2* __restrict
                 __syncthreads();
             }
             const int o = a.nops - 1;
-            form(o, [&](auto kk, auto pp) {
+            auto tail = [&](auto kk, auto pp) {
+                constexpr int K = decltype(kk)::value;
                 f4 v[8];
-                Operands x;
-                read(o, own<decltype(kk)::value, decltype(pp)::value>(address(o)), v);
+                read(o, own<K, decltype(pp)::value>(address(o)), v);
                 __syncthreads();                         // the tile may be overwritten
-                convert<decltype(kk)::value, decltype(pp)::value, false>(x, v, 1.f);
-                apply<decltype(kk)::value, decltype(pp)::value>(lds, a.op[o].image, lane, x, store);
-            });
+                if constexpr (K == 0) {
+#pragma unroll
+                    for (int m = 0; m < 8; ++m) store(m, v[m]);
+                } else {
+                    Operands x;
+                    convert<K, decltype(pp)::value, false>(x, v, 1.f);
+                    apply<K, decltype(pp)::value>(lds, a.op[o].image, lane, x, store);
+                }
+            };
+            if (a.op[o].k == 0) tail(c0{}, std::false_type{});
+            else form(o, tail);
         }
         if (!next) break;
         tb = nb;
@@ -459,6 +475,8 @@ using SplitKernel = void (*)(float2*, SplitK);
 template <int TW, bool ZERO, bool ONE>
 SplitKernel split_kernel_t(int k, int pair)
 {
+    if constexpr (!ONE)
+        if (k == 0) return k_split<TW, ZERO, 0, false, false>;
     if (k == 5) return pair ? k_split<TW, ZERO, 5, true, ONE> : k_split<TW, ZERO, 5, false, ONE>;
     return pair ? k_split<TW, ZERO, 4, true, ONE> : k_split<TW, ZERO, 4, false, ONE>;
 }
@@ -488,6 +506,30 @@ struct SplitLayout {
     int perm[5];
     int pair;
 };
+
+// A parking step (the tile copied to or from LDS before the first or after the
+// last block): lanes, then waves, then accesses by ascending tile bits, so that
+// at any time the workgroup reads or writes one contiguous stretch.  For blocks
+// whose own layout makes half-line accesses (split_narrow): alone on 2^30
+// amplitudes 4.0-4.1 ms without, 3.3 with it after the block, 2.94 with both;
+// for other first and last blocks the trips through LDS cost more than the
+// order gives (30 qubits, depth 14: 25.96 ms without, 27.1 with it in front,
+// 26.9 behind, 28.3 both).
+SplitLayout linear_layout(int t)
+{
+    SplitLayout L;
+    for (int& x : L.lane) x = -1;
+    for (int& x : L.m) x = -1;
+    for (int& x : L.wave) x = -1;
+    for (int u = 0; u < 5; ++u) L.perm[u] = 0;
+    L.pair = 0;
+    int b = 1;
+    for (int i = 0; i < 6; ++i)
+        if (t > 9 || i != 3) L.lane[i] = b++;            // (9 positions: lane bit 3 is spare, as for blocks)
+    for (int i = 0; b < t - 3; ++i) L.wave[i] = b++;
+    for (int i = 0; i < 3; ++i) L.m[i] = b++;
+    return L;
+}
 
 // targets: tile bit of each matrix bit.  Matrix bits: the target at tile bit
 // 0 is b0; of the others the two lowest are b2, b3 (lane bits, so that an
@@ -563,13 +605,46 @@ uint32_t split_chunk(int b)
     return ((1u << c) | (c >= 3 ? 1u << (c % 3) : 0u)) * 16u;
 }
 
+// A block on all of positions 1, 2, 3: an access of a wave then reads or writes
+// 64 contiguous bytes at a time (the two lowest targets are lane bits, the
+// third is not), half a cache line.
+bool split_narrow(int k, const int* pos)
+{
+    int low = 0;
+    for (int j = 0; j < k; ++j)
+        if (pos[j] >= 1 && pos[j] <= 3) low |= 1 << pos[j];
+    return low == 14;
+}
+
+// amplitudes (as bits) from which a lone block's pass is parked or narrowed
+constexpr int kLoneBits = 27, kLoneNarrowBits = 24;
+
 }  // namespace
+
+// Tile width of a pass of one block.  What it costs is the order in which it
+// touches memory: on the block's own layout the waves of a wide tile hold
+// accesses whose addresses agree in the bits that choose the memory channel.
+// Parked on both sides, a 14-position tile is read and written as one stretch
+// of 128 KiB; without that width, short tiles spread over more workgroups do
+// better.  Mean over 12 sets of targets (direct, 13 positions -> direct, 12 ->
+// parked, 13 -> parked, 14): 2^30 amplitudes, 5 qubits 3,482 -> 3,355 -> 3,352 ->
+// 3,178 us, 4 qubits 3,472 -> 3,447 -> 3,332 -> 3,176; 2^25, 5 qubits 124 -> 119 ->
+// 121 -> 122, 4 qubits 116 -> 110 -> 111 -> 114; 2^22 32.1 and 25.4 direct
+// against 35 and 27 parked.
+int split_lone_width(int k, const int* pos, int bits, int t_max)
+{
+    if (bits < kLoneNarrowBits || split_narrow(k, pos)) return t_max;
+    if (bits >= kLoneBits && t_max >= 14) return 14;
+    if (bits >= kLoneBits && k == 4 && t_max >= 13) return 13;
+    return t_max < 12 ? t_max : 12;
+}
 
 hipError_t split_prepare(int t, int lds)
 {
-    for (int v = 0; v < 16; ++v) {
-        const hipError_t e = hipFuncSetAttribute((const void*)split_kernel(t, v & 1, v & 2 ? 5 : 4, (v >> 2) & 1, v & 8),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    for (int v = 0; v < 18; ++v) {
+        const SplitKernel kern = v < 16 ? split_kernel(t, v & 1, v & 2 ? 5 : 4, (v >> 2) & 1, v & 8)
+                                        : split_kernel(t, v & 1, 0, 0, false);
+        const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -579,33 +654,45 @@ hipError_t launch_split(hipStream_t st, void* psi, int t, const int* P, int nops
                         const int* const* pos, const void* const* mats, uint64_t tiles, uint64_t tmask,
                         uint64_t newmask, bool from_e0, double* norm_out, int* norm_blocks, int split_exp)
 {
-    if (t < 9 || t > 14 || nops < 1 || nops > kSplitMaxOps) return hipErrorInvalidValue;
+    if (t < 9 || t > 14 || nops < 1 || nops > kSplitMaxOps - 2) return hipErrorInvalidValue;
+    // sides that go through a parking step
+    const bool wide = std::ldexp((double)tiles, t) >= std::ldexp(1.0, kLoneBits);
+    const bool lone = nops == 1 && wide && (t == 14 || (t == 13 && ks[0] == 4));
+    bool in = lone || split_narrow(ks[0], pos[0]), out = lone || split_narrow(ks[nops - 1], pos[nops - 1]);
+    {
+        int need = (8 << t) + (nops + 2) * 256;
+        for (int o = 0; o < nops; ++o) need += 8 << (2 * ks[o]);
+        if (need > (t >= 14 ? 160 : 80) * 1024) in = out = false;
+    }
     SplitK a{};
     a.tiles = tiles;
     a.tmask = tmask;
-    a.nops = nops;
+    const int steps = nops + in + out;
+    a.nops = steps;
     a.from_e0 = from_e0 ? 1 : 0;
     a.norm_out = norm_out;
     a.scale = std::ldexp(1.0f, split_exp);
     a.unscale = std::ldexp(1.0f, -split_exp);
     int at = 8 << t;
-    for (int o = 0; o < nops; ++o) {
+    for (int o = 0; o < steps; ++o) {
+        const int blk = o - in;
+        const bool park = blk < 0 || blk >= nops;
         int tbit[kMaxDense];
-        for (int j = 0; j < ks[o]; ++j) {
+        for (int j = 0; !park && j < ks[blk]; ++j) {
             int b = 0;
-            while (b < t && P[b] != pos[o][j]) ++b;
+            while (b < t && P[b] != pos[blk][j]) ++b;
             if (b == t) return hipErrorInvalidValue;
             tbit[j] = b;
         }
-        const bool hbm = o == 0 || o == nops - 1;
-        const SplitLayout L = split_layout(t, ks[o], tbit, hbm);
+        const bool hbm = o == 0 || o == steps - 1;
+        const SplitLayout L = park ? linear_layout(t) : split_layout(t, ks[blk], tbit, hbm);
         SplitOp& op = a.op[o];
-        op.mat = (const float2*)mats[o];
-        op.k = ks[o];
+        op.mat = park ? nullptr : (const float2*)mats[blk];
+        op.k = park ? 0 : ks[blk];
         op.pair = L.pair;
         for (int u = 0; u < 5; ++u) op.perm[u] = L.perm[u];
         op.image = at;
-        at += 8 << (2 * ks[o]);
+        if (!park) at += 8 << (2 * ks[blk]);
         for (int b = 0; b < 6; ++b) op.lds_lane[b] = split_chunk(L.lane[b]);
         for (int b = 0; b < 3; ++b) op.lds_m[b] = split_chunk(L.m[b]);
         for (int b = 0; b < 4; ++b) op.lds_wave[b] = split_chunk(L.wave[b]);
@@ -629,7 +716,7 @@ hipError_t launch_split(hipStream_t st, void* psi, int t, const int* P, int nops
                     if ((m >> b) & 1) a.ld_m[m] |= reached(L.m[b]);
             a.z_pair = (newmask >> P[0]) & 1;
         }
-        if (o == nops - 1) {
+        if (o == steps - 1) {
             for (int b = 0; b < 6; ++b) a.st_lane[b] = where(L.lane[b]);
             for (int b = 0; b < 4; ++b) a.st_wave[b] = where(L.wave[b]);
             for (int m = 0; m < 8; ++m)
@@ -638,7 +725,7 @@ hipError_t launch_split(hipStream_t st, void* psi, int t, const int* P, int nops
         }
     }
     a.table = at;
-    const int lds = at + nops * 256;
+    const int lds = at + steps * 256;
     if (lds > 160 * 1024) return hipErrorInvalidValue;
     const int nt = split_lanes(t);
     // persistent: as many workgroups as are resident (sixteen waves per CU,
@@ -650,7 +737,7 @@ hipError_t launch_split(hipStream_t st, void* psi, int t, const int* P, int nops
     const uint64_t cap = 256ull * per_cu;
     if (grid > cap) grid = cap;
     a.tstep = spread_bits(grid, a.tmask);
-    hipLaunchKernelGGL(split_kernel(t, newmask != 0, a.op[0].k, a.op[0].pair, nops == 1), dim3((unsigned)grid), dim3(nt), lds, st, (float2*)psi, a);
+    hipLaunchKernelGGL(split_kernel(t, newmask != 0, a.op[0].k, a.op[0].pair, steps == 1), dim3((unsigned)grid), dim3(nt), lds, st, (float2*)psi, a);
     if (norm_blocks) *norm_blocks = norm_out ? (int)grid : 0;
     return hipGetLastError();
 }

@@ -525,6 +525,10 @@ hipError_t launch_stage(hipStream_t st, void* psi, int nloc, int nops, const int
                         uint64_t* amps_out, int split_exp, int dtype)
 {
     int P[64];
+    if (nops == 1 && split_exp != kNoSplit && ks[0] >= 4 && ks[0] <= 5) {
+        const uint64_t seen = support & (nloc >= 64 ? ~0ull : (1ull << nloc) - 1);
+        t_max = split_lone_width(ks[0], pos[0], __builtin_popcountll(seen), t_max);
+    }
     const int t = stage_positions(nloc, nops, ks, pos, t_max, support, P, dtype);
     if (t < 0) return hipErrorInvalidValue;
     if (dtype && split_exp != kNoSplit) return hipErrorInvalidValue;

@@ -253,3 +253,59 @@ def test_split_block_forms(t, start):
             assert abs(stats[0] - 1.0) <= 1e-6 * len(ops)
         finally:
             sv.destroy_state(h)
+
+
+@pytest.mark.parametrize("start", ["dense", "reset"])
+@pytest.mark.parametrize("t", [9, 10, 12, 13, 14])
+def test_split_parked_blocks(t, start):
+    """Blocks on all of positions 1, 2, 3, whose tiles are parked in LDS on
+    their side of the pass: alone, first, last and both, with and without
+    position 0.  Bound as in test_split_block_forms."""
+    n = t + 5
+    rng = np.random.default_rng(900 + t)
+    a, b, c = ([1, 2, 3, int(x)] for x in rng.choice(np.arange(4, n), size=3, replace=False))
+    other = [4, 5, 6, 7]
+    for seq in [[a], [[0] + a], [a, other], [other, [0] + b], [[0] + a, other, c], [other, a, other], [a, [0] + a]]:
+        psi = W.random_state(n, rng)
+        h, tensor = _ext_state(psi)
+        try:
+            sv.set_option(h, sv.SV_OPT_STAGE, t)
+            if start == "reset":
+                sv.reset(h)
+                psi = orc.zero_state(n)
+            ops = [(list(rng.permutation(qs).tolist()), W.random_unitary(1 << len(qs), rng)) for qs in seq]
+            for qs, u in ops:
+                sv.apply_fused(h, qs, u, "c64")
+            got, stats = sv.reduce_slices(h, np.arange(1 << n, dtype=np.uint64))
+            assert sv.counters(h)["staged_blocks"] == len(ops) and sv.stage_forms(h)["fp32"] == 0
+            assert orc.rel_l2(got, _oracle(psi, ops)) <= 5e-7 * len(ops), (t, seq)
+            assert abs(stats[0] - 1.0) <= 1e-6 * len(ops)
+        finally:
+            sv.destroy_state(h)
+
+
+@pytest.mark.parametrize("n", [24, 27])
+@pytest.mark.parametrize("qs", [[2, 9, 14, 20, 22], [5, 11, 16, 23], [3, 2, 1, 12]])
+@pytest.mark.parametrize("t", [13, 14])
+def test_split_lone_block_large(n, qs, t):
+    """One block on a large state, tiles narrowed or parked, against the same
+    block as a plain fp32 sweep: 5e-7 for the split, as much for the sweep."""
+    torch = _torch()
+    rng = np.random.default_rng(n + len(qs))
+    g = torch.Generator(device="cuda").manual_seed(n)
+    psi = torch.view_as_complex(torch.randn((1 << n, 2), generator=g, device="cuda"))
+    psi /= torch.linalg.vector_norm(psi)
+    u = W.random_unitary(1 << len(qs), rng)
+    outs = []
+    for stage in (t, 0):
+        x = psi.clone()
+        torch.cuda.synchronize()
+        h = sv.create_state_ext(n, 0, "c64", None, x.data_ptr(), x.numel() * 8, keep=True)
+        try:
+            sv.set_option(h, sv.SV_OPT_STAGE, stage)
+            sv.apply_fused(h, qs, u, "c64")
+            sv.sync_state(h)
+        finally:
+            sv.destroy_state(h)
+        outs.append(x)
+    assert float(torch.linalg.vector_norm(outs[0] - outs[1])) <= 1e-6
