@@ -131,7 +131,9 @@ hipError_t launch_dense_mfma_batch(hipStream_t st, int k, bool fold, bool staged
 // ---------------------------------------------------------------------------
 typedef double d4 __attribute__((ext_vector_type(4)));
 
-template <int K, bool FOLD>
+typedef double dd2 __attribute__((ext_vector_type(2)));
+
+template <int K, bool FOLD, bool NT>
 __device__ __forceinline__ void dense64_tiles(const Sweep& a, uint64_t t0, uint64_t step, uint64_t t_end)
 {
     constexpr int D = 1 << K, RB = D / 16, NE = D / 4;
@@ -155,13 +157,18 @@ __device__ __forceinline__ void dense64_tiles(const Sweep& a, uint64_t t0, uint6
         for (int u = 2; u < K; ++u)
             if ((e >> (u - 2)) & 1) off[e] |= bit[u];
     }
+    auto take = [&](uint64_t i) {
+        if (!NT) return psi[i];
+        const dd2 w = __builtin_nontemporal_load((const dd2*)(psi + i));
+        return double2{w.x, w.y};
+    };
     auto base_of = [&](uint64_t t) { return group_base<K>(a, t * 16 + j) | lane_off; };
     double2 xn[NE];
     uint64_t nbase = 0;
     if (t0 < t_end) {
         nbase = base_of(t0);
 #pragma unroll
-        for (int e = 0; e < NE; ++e) xn[e] = psi[nbase + off[e]];
+        for (int e = 0; e < NE; ++e) xn[e] = take(nbase + off[e]);
     }
     // A[lane % 16][lane / 16] of each product: row 16 rb + j, column 4 e + g
     double2 A[RB][NE];
@@ -185,7 +192,7 @@ __device__ __forceinline__ void dense64_tiles(const Sweep& a, uint64_t t0, uint6
         if (t + step < t_end) {
             nbase = base_of(t + step);
 #pragma unroll
-            for (int e = 0; e < NE; ++e) xn[e] = psi[nbase + off[e]];
+            for (int e = 0; e < NE; ++e) xn[e] = take(nbase + off[e]);
         }
         __builtin_amdgcn_sched_barrier(0);               // the next unit's loads stay ahead of the products
         // Ar xr, Ai xi, Ai xr and Ar xi are summed on their own: half as many
@@ -216,16 +223,17 @@ __device__ __forceinline__ void dense64_tiles(const Sweep& a, uint64_t t0, uint6
                     yi = yr * p.y + yi * p.x;
                     yr = tr;
                 }
-                psi[base + o] = double2{yr, yi};
+                if (NT) __builtin_nontemporal_store(dd2{yr, yi}, (dd2*)(psi + base + o));
+                else psi[base + o] = double2{yr, yi};
             }
     }
 }
 
-template <int K, bool FOLD>
+template <int K, bool FOLD, bool NT>
 __global__ __launch_bounds__(256, 2) void k_dense64_mfma(Sweep a)
 {
     const uint64_t wave = (uint64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    dense64_tiles<K, FOLD>(a, wave, (uint64_t)gridDim.x * 4, a.groups / 16);
+    dense64_tiles<K, FOLD, NT>(a, wave, (uint64_t)gridDim.x * 4, a.groups / 16);
 }
 
 template <int K, bool FOLD>
@@ -236,29 +244,40 @@ __global__ __launch_bounds__(256, 2) void k_dense64_mfma_batch(const Sweep* __re
     const uint64_t b_end = (i + 1 < nitems) ? items[i + 1].block0 : gridDim.x;
     const uint64_t nb = b_end - a.block0;
     const uint64_t wave = (blockIdx.x - a.block0) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    dense64_tiles<K, FOLD>(a, wave, nb * 4, a.groups / 16);
+    dense64_tiles<K, FOLD, false>(a, wave, nb * 4, a.groups / 16);
 }
 
 hipError_t launch_dense64_mfma(hipStream_t st, const Sweep& a)
 {
     const uint64_t tiles = a.groups / 16;
     if (tiles < 1) return hipErrorInvalidValue;
-    // one wave per SIMD at k = 5 (170 registers, 64 products a unit), two at
-    // k = 4: 2^26 amplitudes at k = 5 take 384-400 us with 256 workgroups,
-    // 404-415 with 512; 2^27 at k = 4 803-843 us with either, 845-950 with more
+    // Beyond the 256 MB cache non-temporal accesses and one wave per SIMD; below,
+    // plain ones, and two waves at k = 4 (k = 5: 170 registers, 64 products a
+    // unit).  Mean of 12 sets of targets (plain, 512 / 256 workgroups at k = 4 / 5
+    // -> non-temporal, the same -> non-temporal, 256): 2^27 amplitudes, k = 4 906 ->
+    // 838 -> 795 us (k_dense 854), k = 5 836 -> 790 (k_dense 972); 2^24, k = 4 96 ->
+    // 109 -> 112 (102), k = 5 112 -> 119 (151); 2^16, k = 4 19.3 a call (25.0).
     uint64_t g = (tiles + 3) / 4;
-    const uint64_t cap = a.k == 5 ? 256 : 512;
+    const bool nt = (tiles << (a.k + 4)) >= (1ull << 25);
+    const uint64_t cap = a.k == 5 || nt ? 256 : 512;
     if (g > cap) g = cap;
     const dim3 grid((unsigned)g), block(256);
+#define SV_D64(KK)                                                                                    \
+    if (nt) {                                                                                         \
+        if (a.ftab) hipLaunchKernelGGL((k_dense64_mfma<KK, true, true>), grid, block, 0, st, a);      \
+        else hipLaunchKernelGGL((k_dense64_mfma<KK, false, true>), grid, block, 0, st, a);            \
+    } else {                                                                                          \
+        if (a.ftab) hipLaunchKernelGGL((k_dense64_mfma<KK, true, false>), grid, block, 0, st, a);     \
+        else hipLaunchKernelGGL((k_dense64_mfma<KK, false, false>), grid, block, 0, st, a);           \
+    }
     if (a.k == 4) {
-        if (a.ftab) hipLaunchKernelGGL((k_dense64_mfma<4, true>), grid, block, 0, st, a);
-        else hipLaunchKernelGGL((k_dense64_mfma<4, false>), grid, block, 0, st, a);
+        SV_D64(4)
     } else if (a.k == 5) {
-        if (a.ftab) hipLaunchKernelGGL((k_dense64_mfma<5, true>), grid, block, 0, st, a);
-        else hipLaunchKernelGGL((k_dense64_mfma<5, false>), grid, block, 0, st, a);
+        SV_D64(5)
     } else {
         return hipErrorInvalidValue;
     }
+#undef SV_D64
     return hipGetLastError();
 }
 

@@ -843,3 +843,38 @@ def test_c128_staged_block_forms(t, start):
             assert abs(stats[0] - orc.norm(ref)) <= 1e-14 * len(ks)
         finally:
             sv.destroy_state(h)
+
+
+@pytest.mark.parametrize("qs,diag", [([2, 9, 17, 24], None), ([0, 1, 2, 3, 4], [5, 24]), ([24, 11, 3, 20, 7], None),
+                                     ([6, 0, 23, 12], [12, 1, 18])])
+def test_dense64_large_state(qs, diag):
+    """Complex128 sweeps on the matrix cores on a state beyond the last-level
+    cache (non-temporal accesses), alone and with a folded diagonal, against
+    the product done by torch in complex128: 2^-53 sqrt(32) for the sums with a
+    factor 4 for the complex products on both sides."""
+    torch = _torch()
+    n, k = 25, len(qs)
+    rng = np.random.default_rng(k + qs[0])
+    g = torch.Generator(device="cuda").manual_seed(n + k)
+    psi = torch.view_as_complex(torch.randn((1 << n, 2), generator=g, device="cuda", dtype=torch.float64))
+    psi /= torch.linalg.vector_norm(psi)
+    u = W.random_unitary(1 << k, rng)
+    axes = [n - 1 - q for q in reversed(qs)]                    # matrix bit j = qubit qs[j]
+    x = torch.movedim(psi.view([2] * n), axes, list(range(k))).reshape(1 << k, -1)
+    ref = torch.from_numpy(u).cuda() @ x
+    ref = torch.movedim(ref.view([2] * n), list(range(k)), axes).reshape(-1)
+    if diag:
+        ph = W.random_phases(1 << len(diag), rng)
+        idx = torch.arange(1 << n, device="cuda")
+        c = sum(((idx >> q) & 1) << j for j, q in enumerate(diag))
+        ref = ref * torch.from_numpy(ph).cuda()[c]
+    torch.cuda.synchronize()
+    h = sv.create_state_ext(n, 0, "c128", None, psi.data_ptr(), psi.numel() * 16, keep=True)
+    try:
+        sv.apply_fused(h, qs, u, "c128")
+        if diag:
+            sv.apply_diag(h, diag, ph, "c128")
+        sv.sync_state(h)
+    finally:
+        sv.destroy_state(h)
+    assert float(torch.linalg.vector_norm(psi - ref)) <= 8 * 2.0 ** -53 * np.sqrt(32)
