@@ -994,7 +994,7 @@ def bench_single(args) -> int:
                          "frac": round(gbs / HBM_PEAK_GBS, 4), "avg_launch_ms": round(avg, 4),
                          "bytes_per_launch": by,
                          "traffic": profile_traffic("single_block_30q_traffic.json",
-                                                    "paper_1910_09534_amd/csrc/sv_stage.hip")}}
+                                                    "paper_1910_09534_amd/csrc/sv_split.hip")}}
     print(json.dumps(line), flush=True)
     return 0
 
