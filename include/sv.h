@@ -279,7 +279,8 @@ enum {
                               form and 512 in the fp32 form, holding the
                               whole LDS; a pass widens its tile with free positions
                               to the widest width the LDS holds for its blocks'
-                              matrices; in the split-fp16 form 14 measured fastest
+                              matrices, a large lone block may take a narrower
+                              one; in the split-fp16 form 14 measured fastest
                               for states of 2^23 to 2^30 amplitudes, in the fp32 form
                               13 at 2^30; complex128: eight waves per CU, tiles
                               of at most 13 positions, products on the FP64 matrix

@@ -39,6 +39,9 @@ double sv::op_growth(const void* m, int k, size_t amp, bool* unit)
 {
     // G = M^H M (Hermitian: the upper triangle, in fp32, is enough for a
     // tolerance of 1e-3); ||M||_2^2 = lambda_max(G) <= max_r sum_c |G_rc|
+    // Four rows of M at a time, each sum in the order of the rows: loads and
+    // stores of the sums bound the loop (k = 6: 27.6 us; a row at a time 31.6 or
+    // 39.2, by the place that the loop has in the library).
     constexpr int DM = 1 << kMaxDense;
     thread_local float re[DM * DM], im[DM * DM], gr[DM * DM], gi[DM * DM];
     thread_local double row[DM];
@@ -53,16 +56,25 @@ double sv::op_growth(const void* m, int k, size_t amp, bool* unit)
         }
         gr[i] = gi[i] = 0.f;
     }
-    for (int x = 0; x < D; ++x) {
+    constexpr int U = 4;
+    for (size_t i = (size_t)D * D; i < (size_t)U * D; ++i) re[i] = im[i] = 0.f;   // D = 2: two rows of zeros
+    for (int x = 0; x < D; x += U) {
         const float* ar = &re[(size_t)x * D];
         const float* ai = &im[(size_t)x * D];
         for (int r = 0; r < D; ++r) {
-            const float cr = ar[r], ci = -ai[r];
+            float cr[U], ci[U];
+            for (int u = 0; u < U; ++u) cr[u] = ar[u * D + r], ci[u] = -ai[u * D + r];
             float* pr = &gr[(size_t)r * D];
             float* pi = &gi[(size_t)r * D];
             for (int c = r; c < D; ++c) {
-                pr[c] += cr * ar[c] - ci * ai[c];
-                pi[c] += cr * ai[c] + ci * ar[c];
+                float sr = pr[c], si = pi[c];
+                for (int u = 0; u < U; ++u) {
+                    const float br = ar[u * D + c], bi = ai[u * D + c];
+                    sr += cr[u] * br - ci[u] * bi;
+                    si += cr[u] * bi + ci[u] * br;
+                }
+                pr[c] = sr;
+                pi[c] = si;
             }
         }
     }
@@ -273,10 +285,10 @@ int run_ops(sv_state* h, hipStream_t st, void** psi, void* alt, int nloc, uint64
     double bnd = h->amp_bound;
     for (size_t i = 0; i < nops; ++i) {
         const Op& op = h->ops[i];
-        // a run of consecutive 4/5-qubit complex64 blocks whose targets fit in
+        // a run of consecutive 4/5-qubit blocks whose targets fit in
         // one LDS tile goes through a single staged HBM pass
         // (complex64 with the matrix-core sweeps on from k = 4; complex128
-        // always: its single sweeps run on the vector units)
+        // always)
         const int stage_t = h->stage_t;
         if (op.kind == OP_DENSE && stage_t >= 9 && (h->dtype != 0 || h->mfma_min_k == 4) &&
             (op.k == 4 || op.k == 5)) {

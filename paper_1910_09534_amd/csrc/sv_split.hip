@@ -25,7 +25,9 @@
 // (one address computation, no hazard between waves), and the first block of
 // a run can take its operands straight from HBM and the last one can store
 // its results straight to HBM: a run of n blocks makes n - 1 trips through
-// LDS instead of n + 1, and a lone block none.
+// LDS instead of n + 1, and a lone block none.  Where a block's own layout is a
+// poor order for the memory, a parking step takes its side of the pass
+// (linear_layout, split_lone_width).
 //
 // The two amplitudes of an access are two groups when position 0 is no
 // target of the block, and two matrix columns (bit b0) when it is.
