@@ -320,17 +320,23 @@ hipError_t launch_dense_batch(hipStream_t st, int dtype, int k, bool fold, const
 // diagonal op
 // ---------------------------------------------------------------------------
 // A workgroup takes one chunk of amplitudes (256 lanes, one 16-byte access
-// each).  The gate's positions inside a chunk select an entry of a sub-table
-// in LDS, by parts that a lane puts together from its lane bits; the
-// positions above are the same for the whole chunk and choose which part of
-// the table the sub-table holds.
+// each).  A lane puts the gate's positions inside a chunk together from its
+// lane bits; the positions above are the same for the whole chunk.  Beyond
+// 256 MiB of state they choose the part of the table that the workgroup copies
+// to a sub-table in LDS, and the lanes read that.  DIRECT: the lanes read the
+// table itself, where the sub-table would be as large as the chunk (nothing is
+// read twice; 2^27 complex64 amplitudes, m = 12 on the lowest positions 490 ->
+// 381 us), and up to 256 MiB, where the copy and its barrier only lengthen the
+// chain (with upload and wait, complex64: 2^16, m = 12 36.2 -> 35.9, 2^24, m = 12
+// 78 -> 75).  NT: non-temporal accesses, beyond 256 MiB only: the memory-side
+// cache holds a state up to there (2^24 complex128, m = 3: 101 us with them, 91
+// without; 2^25: 183 both).
 //
 // Bound by HBM: 2^28 complex64 amplitudes, m = 6 take 680-690 us (6.2-6.3 TB/s)
 // against 970-987 with one amplitude per access and its table index put
 // together from the whole address, 2^27 complex128 687 against 722.  Chunks of
 // 2, 4 and 8 accesses a lane take 690, 726 and 797 us, persistent workgroups
-// 810-850.  m = 12 on the lowest positions (a sub-table as large as its chunk)
-// 951 against 1,071 us.
+// 810-850.
 struct DiagK {
     uint64_t count;                          // amplitudes
     uint64_t idx_offset;
@@ -341,7 +347,7 @@ struct DiagK {
     uint32_t high_tab[kMaxDiag];
 };
 
-template <typename R>
+template <typename R, bool DIRECT, bool NT>
 __global__ __launch_bounds__(256) void k_diag(typename Vec2<R>::T* __restrict__ psi,
                                               const typename Vec2<R>::T* __restrict__ table, DiagK a)
 {
@@ -354,30 +360,36 @@ __global__ __launch_bounds__(256) void k_diag(typename Vec2<R>::T* __restrict__ 
     const uint64_t base = (uint64_t)blockIdx.x * (256 * E), at = base + (uint64_t)tid * E;
     const bool in = at < a.count;
     A x{};
-    if (in) x = __builtin_nontemporal_load((const A*)(psi + at));
+    if (in) x = NT ? __builtin_nontemporal_load((const A*)(psi + at)) : *(const A*)(psi + at);
     uint32_t hi = 0;
     for (int k = 0; k < a.nhigh; ++k)
         if (((base + a.idx_offset) >> a.high_pos[k]) & 1) hi |= a.high_tab[k];
-    for (int s = tid; s < (1 << a.nlow); s += 256) {
-        uint32_t t = hi;
-        for (int k = 0; k < a.nlow; ++k)
-            if ((s >> k) & 1) t |= a.sub_tab[k];
-        sub[s] = table[t];
-    }
-    uint32_t li = 0;
+    uint32_t li = DIRECT ? hi : 0;
 #pragma unroll
     for (int b = 0; b < 8; ++b)
         if ((tid >> b) & 1) li |= a.lane_sub[b];
-    __syncthreads();
+    const V* tab = DIRECT ? table : sub;
+    if (!DIRECT) {
+        for (int s = tid; s < (1 << a.nlow); s += 256) {
+            uint32_t t = hi;
+            for (int k = 0; k < a.nlow; ++k)
+                if ((s >> k) & 1) t |= a.sub_tab[k];
+            sub[s] = table[t];
+        }
+        __syncthreads();
+    }
     A y;
 #pragma unroll
     for (int q = 0; q < E; ++q) {
-        const V p = sub[q ? li | a.pair_sub : li];
+        const V p = tab[q ? li | a.pair_sub : li];
         const R vr = x[2 * q], vi = x[2 * q + 1];
         y[2 * q] = vr * p.x - vi * p.y;
         y[2 * q + 1] = vr * p.y + vi * p.x;
     }
-    if (in) __builtin_nontemporal_store(y, (A*)(psi + at));
+    if (in) {
+        if (NT) __builtin_nontemporal_store(y, (A*)(psi + at));
+        else *(A*)(psi + at) = y;
+    }
 }
 
 hipError_t launch_diag(hipStream_t st, void* psi, int dtype, int nloc, uint64_t idx_offset,
@@ -386,6 +398,10 @@ hipError_t launch_diag(hipStream_t st, void* psi, int dtype, int nloc, uint64_t 
     if (d.m < 1 || d.m > kMaxDiag) return hipErrorInvalidValue;
     const int pb = dtype ? 0 : 1;            // position 0 is inside an access (complex64)
     const int cb = pb + 8;                   // positions inside a chunk
+    int low = 0;                             // gate positions inside a chunk
+    for (int j = 0; j < d.m; ++j) low += d.pos[j] < cb && d.pos[j] < nloc;
+    // up to 256 MiB the state stays in the memory-side cache between calls
+    const bool cached = nloc <= 24 + pb, direct = cached || low == cb;
     DiagK a{};
     a.count = 1ull << nloc;
     a.idx_offset = idx_offset;
@@ -399,20 +415,20 @@ hipError_t launch_diag(hipStream_t st, void* psi, int dtype, int nloc, uint64_t 
                 a.high_tab[a.nhigh++] = bit;
                 continue;
             }
-            const uint32_t s = 1u << a.nlow;
+            const uint32_t s = direct ? bit : 1u << a.nlow;
             a.sub_tab[a.nlow++] = bit;
             if (p < pb) a.pair_sub = s;
             else a.lane_sub[p - pb] = s;
         }
     const uint64_t grid = nloc > cb ? 1ull << (nloc - cb) : 1;
     if (grid > 0x7fffffffull) return hipErrorInvalidValue;
-    const size_t lds = ((size_t)1 << a.nlow) * (dtype ? 16 : 8);
+    const size_t lds = direct ? 0 : ((size_t)1 << a.nlow) * (dtype ? 16 : 8);
+    const auto f32 = cached ? k_diag<float, true, false> : direct ? k_diag<float, true, true> : k_diag<float, false, true>;
+    const auto f64 = cached ? k_diag<double, true, false> : direct ? k_diag<double, true, true> : k_diag<double, false, true>;
     if (dtype == 0)
-        hipLaunchKernelGGL(k_diag<float>, dim3((unsigned)grid), dim3(256), lds, st, (float2*)psi,
-                           (const float2*)d.table, a);
+        hipLaunchKernelGGL(f32, dim3((unsigned)grid), dim3(256), lds, st, (float2*)psi, (const float2*)d.table, a);
     else
-        hipLaunchKernelGGL(k_diag<double>, dim3((unsigned)grid), dim3(256), lds, st, (double2*)psi,
-                           (const double2*)d.table, a);
+        hipLaunchKernelGGL(f64, dim3((unsigned)grid), dim3(256), lds, st, (double2*)psi, (const double2*)d.table, a);
     return hipGetLastError();
 }
 

@@ -878,3 +878,39 @@ def test_dense64_large_state(qs, diag):
     finally:
         sv.destroy_state(h)
     assert float(torch.linalg.vector_norm(psi - ref)) <= 8 * 2.0 ** -53 * np.sqrt(32)
+
+
+@pytest.mark.parametrize("n,dtype", [(25, "c64"), (26, "c64"), (24, "c128"), (25, "c128")])
+def test_diag_large_state(n, dtype):
+    """Diagonal gates on both sides of the size up to which a state's lanes
+    read the table themselves, with few, all and none of a workgroup's positions
+    taken.  One complex product per amplitude: 2 eps."""
+    import torch
+
+    rng = np.random.default_rng(n)
+    real = torch.float32 if dtype == "c64" else torch.float64
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    psi = torch.randn(1 << n, 2, dtype=real, device="cuda", generator=gen)
+    index = torch.arange(1 << n, device="cuda", dtype=torch.int32)
+    torch.cuda.synchronize()
+    chunk = 9 if dtype == "c64" else 8
+    for qs in ([0, 3, n - 1], list(range(chunk)) + [12, n - 1], list(range(chunk, chunk + 4)),
+               list(range(1, 12))):
+        qs = [int(q) for q in rng.permutation(qs)]
+        before = psi.clone()
+        torch.cuda.synchronize()
+        h = sv.create_state_ext(n, 0, dtype, None, psi.data_ptr(), psi.numel() * psi.element_size(), keep=True)
+        try:
+            ph = W.random_phases(1 << len(qs), rng)
+            sv.apply_diag(h, qs, ph, dtype)
+            sv.sync_state(h)
+        finally:
+            sv.destroy_state(h)
+        at = torch.zeros_like(index)
+        for j, q in enumerate(qs):
+            at |= ((index >> q) & 1) << j
+        table = torch.from_numpy(ph.astype(np.complex64) if dtype == "c64" else ph).cuda().to(torch.complex128)
+        ref = torch.view_as_complex(before.double()) * table[at.long()]
+        got = torch.view_as_complex(psi.double())
+        rel = ((got - ref).abs().square().sum() / ref.abs().square().sum()).sqrt().item()
+        assert rel <= (2.0 ** -23 if dtype == "c64" else 2.0 ** -52), qs
