@@ -15,6 +15,7 @@
 // base + l); the group counter is spread over the non-target bit positions
 // in ascending order, so for targets above bit 5 the 64 lanes of one load
 // instruction read 64 consecutive amplitudes (512 B for complex64).
+#include <algorithm>
 #include <cstring>
 
 #include "sv_device.h"
@@ -403,8 +404,6 @@ hipError_t launch_diag(hipStream_t st, void* psi, int dtype, int nloc, uint64_t 
     // up to 256 MiB the state stays in the memory-side cache between calls
     const bool cached = nloc <= 24 + pb, direct = cached || low == cb;
     DiagK a{};
-    a.count = 1ull << nloc;
-    a.idx_offset = idx_offset;
     for (int p = 0; p < 64; ++p)
         for (int j = 0; j < d.m; ++j) {
             if (d.pos[j] != p) continue;
@@ -421,15 +420,24 @@ hipError_t launch_diag(hipStream_t st, void* psi, int dtype, int nloc, uint64_t 
             else a.lane_sub[p - pb] = s;
         }
     const uint64_t grid = nloc > cb ? 1ull << (nloc - cb) : 1;
-    if (grid > 0x7fffffffull) return hipErrorInvalidValue;
     const size_t lds = direct ? 0 : ((size_t)1 << a.nlow) * (dtype ? 16 : 8);
     const auto f32 = cached ? k_diag<float, true, false> : direct ? k_diag<float, true, true> : k_diag<float, false, true>;
     const auto f64 = cached ? k_diag<double, true, false> : direct ? k_diag<double, true, true> : k_diag<double, false, true>;
-    if (dtype == 0)
-        hipLaunchKernelGGL(f32, dim3((unsigned)grid), dim3(256), lds, st, (float2*)psi, (const float2*)d.table, a);
-    else
-        hipLaunchKernelGGL(f64, dim3((unsigned)grid), dim3(256), lds, st, (double2*)psi, (const double2*)d.table, a);
-    return hipGetLastError();
+    // a launch takes fewer than 2^32 work items: 32 GiB of state each, whose
+    // offset adds to the slice's
+    const uint64_t part = std::min<uint64_t>(grid, 1ull << 23);
+    for (uint64_t g = 0; g < grid; g += part) {
+        const uint64_t at = g << cb;
+        a.idx_offset = idx_offset + at;
+        a.count = std::min<uint64_t>(1ull << nloc, part << cb);
+        if (dtype == 0)
+            hipLaunchKernelGGL(f32, dim3((unsigned)part), dim3(256), lds, st, (float2*)psi + at, (const float2*)d.table, a);
+        else
+            hipLaunchKernelGGL(f64, dim3((unsigned)part), dim3(256), lds, st, (double2*)psi + at, (const double2*)d.table, a);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 // ---------------------------------------------------------------------------

@@ -259,3 +259,37 @@ def test_permute_full_size_preserves_amplitudes(dtype, n):
             assert np.array_equal(got, ref)
     finally:
         st.close()
+
+
+@pytest.mark.parametrize("dtype,n", [("c64", 33), ("c128", 32)])
+def test_diagonal_beyond_one_launch(dtype, n):
+    """A diagonal gate on a 64 GiB state, more work items than one launch
+    takes: a product state of seven qubits, two of them in the upper half,
+    against the exact product.  Ten roundings of a complex product, 2 eps each."""
+    _torch()
+    rng = np.random.default_rng(n)
+    put = [0, 3, 8, 9, 20, n - 2, n - 1]
+    gate = [n - 1, 0, 9, n - 2, 20]
+    st = sv.State(n, 0, dtype)
+    try:
+        ones = {}
+        for q in put:
+            m = W.random_unitary(2, rng)
+            st.fused([q], m)
+            ones[q] = m[:, 0]
+        ph = W.random_phases(1 << len(gate), rng)
+        sv.apply_diag(st.h, gate, ph, dtype)
+        bits = np.array([sum(((i >> j) & 1) << q for j, q in enumerate(put)) for i in range(1 << len(put))],
+                        dtype=np.uint64)
+        got = st.gather(bits)
+        zero = st.gather(bits ^ np.uint64(1 << 12))
+    finally:
+        st.close()
+    ref = np.ones(len(bits), dtype=np.complex128)
+    for q in put:
+        ref *= ones[q][((bits >> np.uint64(q)) & np.uint64(1)).astype(int)]
+    at = sum((((bits >> np.uint64(q)) & np.uint64(1)).astype(int) << j) for j, q in enumerate(gate))
+    ref *= ph[at]
+    eps = 2.0 ** -24 if dtype == "c64" else 2.0 ** -53
+    assert orc.rel_l2(got, ref) <= 20 * eps
+    assert np.count_nonzero(zero) == 0

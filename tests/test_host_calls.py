@@ -1,0 +1,91 @@
+"""The library's host side on a machine without a GPU: libsv.so in a process
+of its own whose HIP calls go to the stand-in runtime of fake_hip.cpp.  What
+the stand-in sees is checked: launches within HIP's documented limits at every
+size that fits the device, and what is still running when a call fails.  No
+kernel runs, so results are the GPU tests' matter."""
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
+
+PRELUDE = """
+import ctypes, sys
+F = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)     # ahead of libsv.so's own runtime
+F.fake_log.restype = ctypes.c_char_p
+import numpy as np
+from paper_1910_09534_amd import sv
+
+def log():
+    return F.fake_log().decode().splitlines()
+
+def unitary(k, seed=0):
+    r = np.random.default_rng(seed)
+    return np.linalg.qr(r.normal(size=(2 ** k, 2 ** k)) + 1j * r.normal(size=(2 ** k, 2 ** k)))[0]
+
+def code_of(f, *a):
+    try:
+        f(*a)
+    except sv.SVError as e:
+        return e.code
+    return sv.SV_OK
+"""
+
+
+@pytest.fixture(scope="session")
+def fake_hip(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("fake") / "fake_hip.so")
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__",
+                           "-I", os.path.join(ROCM, "include"), os.path.join(HERE, "fake_hip.cpp"), "-o", out])
+    return out
+
+
+def run(fake_hip, body):
+    p = subprocess.run([sys.executable, "-c", PRELUDE + textwrap.dedent(body), fake_hip], cwd=ROOT,
+                       capture_output=True, text=True, timeout=300)
+    assert p.returncode == 0, p.stdout[-4000:] + p.stderr[-4000:]
+
+
+@pytest.mark.parametrize("dtype,sizes", [("c64", (1, 5, 12, 30, 32, 33, 34)), ("c128", (1, 5, 12, 30, 31, 32, 33))])
+def test_resident_operations_at_every_size(fake_hip, dtype, sizes):
+    """Every operation of a resident state is launched, up to the states that
+    fill the device (a launch takes fewer than 2^32 work items)."""
+    run(fake_hip, f"""
+    for n in {sizes}:
+        for op in ("diag1", "diag3", "k1", "k2", "k3", "k4", "k5", "permute", "reduce"):
+            h = sv.create_state(n, 0, "{dtype}")
+            if op.startswith("diag"):
+                q = sorted({{0, n // 2, n - 1}})[:int(op[4])]
+                sv.apply_diag(h, q, np.ones(1 << len(q)), "{dtype}")
+            elif op.startswith("k"):
+                k = min(int(op[1]), n)
+                sv.apply_fused(h, list(range(n - k, n)), unitary(k), "{dtype}")
+            elif op == "permute":
+                sv.apply_fused(h, [0], unitary(1), "{dtype}")
+                if n <= 30:
+                    sv.sync_state(h)
+                    sv.permute_qubits(h, list(range(n))[::-1])
+            else:
+                sv.reduce_slices(h, np.arange(2, dtype=np.uint64))
+            sv.sync_state(h)
+            sv.destroy_state(h)
+    assert not [x for x in log() if x.startswith("refused")]
+    """)
+
+
+@pytest.mark.parametrize("dtype,n", [("c64", 32), ("c64", 33), ("c64", 34), ("c128", 33)])
+def test_diagonal_covers_large_states(fake_hip, dtype, n):
+    """The workgroups of a diagonal gate's launches cover the state once."""
+    run(fake_hip, f"""
+    h = sv.create_state({n}, 0, "{dtype}")
+    F.fake_clear()
+    sv.apply_diag(h, [0, 9, {n} - 1], np.ones(8), "{dtype}")
+    sv.sync_state(h)
+    grids = [int(x.split(" grid ")[1].split()[0]) for x in log() if x.startswith("launch") and "k_diag" in x]
+    assert sum(grids) * 256 * (2 if "{dtype}" == "c64" else 1) == 1 << {n}, grids
+    """)
