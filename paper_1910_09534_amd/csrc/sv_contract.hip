@@ -463,7 +463,8 @@ __global__ __launch_bounds__(SK > 1 ? 64 * SK : 256) void k_contract_full(
     const int lane = threadIdx.x & 63;
     const int li = lane & 15, lk = lane >> 4;
     // grouped order, as above: the waves of a workgroup share a t1 panel
-    const uint32_t wt = SK > 1 ? blockIdx.x : blockIdx.x * 4 + wave;
+    const uint32_t wg = blockIdx.y * gridDim.x + blockIdx.x;
+    const uint32_t wt = SK > 1 ? wg : wg * 4 + wave;
     if (wt >= tiles_m * tiles_n) return;
     const uint32_t per = group * tiles_n;
     const uint32_t g = wt / per, r = wt % per;
@@ -558,8 +559,12 @@ hipError_t launch_full_tiles(hipStream_t st, const void* t1, const void* t2, voi
     if (tm * tn > 0xfffffff0ull) return hipErrorInvalidValue;
     const uint32_t group = tm < 16 ? (uint32_t)tm : 16;
     const uint64_t wgs = SK > 1 ? tm * tn : (tm * tn + 3) / 4;
-    hipLaunchKernelGGL((k_contract_full<T, RB, CB, KU, SK>), dim3((unsigned)wgs), dim3(SK > 1 ? 64 * SK : 256), 0, st,
-                       (const V*)t1, (const V*)t2, (V*)out, n1, n2, e, (uint32_t)tm, (uint32_t)tn, group);
+    // a grid dimension takes fewer than 2^32 work items (2^34 outputs with a
+    // side of 16 have more); both are powers of two
+    const uint64_t gx = std::min<uint64_t>(wgs, 1u << 20);
+    hipLaunchKernelGGL((k_contract_full<T, RB, CB, KU, SK>), dim3((unsigned)gx, (unsigned)(wgs / gx)),
+                       dim3(SK > 1 ? 64 * SK : 256), 0, st, (const V*)t1, (const V*)t2, (V*)out, n1, n2, e,
+                       (uint32_t)tm, (uint32_t)tn, group);
     return hipGetLastError();
 }
 

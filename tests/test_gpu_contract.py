@@ -107,6 +107,36 @@ def test_contract_tile_choice(n1, n2, e, fp32, scale):
     assert np.abs(got - ref).max() <= 1e-5 * np.sqrt(1 << e) * scale
 
 
+@pytest.mark.parametrize("n1,n2", [(4, 30), (30, 4)])
+def test_contract_more_outputs_than_one_grid_dimension(n1, n2):
+    """2^34 outputs with a side of 16: more work items than a grid dimension
+    takes.  Stretches of outputs at both ends and in between are checked, the
+    bound as above."""
+    torch = _torch()
+    e, big = 2, max(n1, n2)
+    gen = torch.Generator(device="cuda").manual_seed(n1)
+    t1 = torch.randn((1 << e) << n1, dtype=torch.complex64, device="cuda", generator=gen)
+    t2 = torch.randn((1 << e) << n2, dtype=torch.complex64, device="cuda", generator=gen)
+    out = torch.empty(1 << (n1 + n2), dtype=torch.complex64, device="cuda")
+    sv.contract(t1.data_ptr(), t2.data_ptr(), out.data_ptr(), n1, n2, e, "c64",
+                torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    m1, m2, o = t1.view(1 << e, 1 << n1), t2.view(1 << e, 1 << n2), out.view(1 << n2, 1 << n1)
+    width = 1 << 16
+    try:
+        for at in [0, 1 << 20, (1 << 29) - width // 2, (1 << big) - width] + [3 << k for k in range(17, 28)]:
+            part = slice(at, at + width)
+            if n2 == big:
+                ref, got = m2[:, part].cpu().numpy().T.astype(np.complex128) @ m1.cpu().numpy(), o[part]
+            else:
+                ref, got = m2.cpu().numpy().T.astype(np.complex128) @ m1[:, part].cpu().numpy(), o[:, part]
+            got = got.cpu().numpy().astype(np.complex128)
+            assert orc.rel_l2(got.ravel(), ref.ravel()) <= 4 * 2.0 ** -24 * np.sqrt(1 << e), at
+    finally:
+        del t1, t2, out, m1, m2, o
+        torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("s1,s2", [(1e-6, 1.0), (1.0, 3e5), (1e-15, 1e-12), (1e10, 1e-10)])
 def test_contract_split_accuracy_independent_of_scale(s1, s2):
     """The split-fp16 form scales each tensor from its own largest component:

@@ -89,3 +89,20 @@ def test_diagonal_covers_large_states(fake_hip, dtype, n):
     grids = [int(x.split(" grid ")[1].split()[0]) for x in log() if x.startswith("launch") and "k_diag" in x]
     assert sum(grids) * 256 * (2 if "{dtype}" == "c64" else 1) == 1 << {n}, grids
     """)
+
+
+@pytest.mark.parametrize("dtype", ["c64", "c128"])
+def test_contractions_at_every_size(fake_hip, dtype):
+    """Every contraction that fits the device is launched, in both forms."""
+    run(fake_hip, f"""
+    amp = 8 if "{dtype}" == "c64" else 16
+    at = 1 << 44                                    # (never read: no kernel runs)
+    for n1 in range(36):
+        for n2 in range(36):
+            for e in range(13):
+                if amp * (2 ** (n1 + n2) + 2 ** (n1 + e) + 2 ** (n2 + e)) > 288e9:
+                    continue
+                for fp32 in (False, True) if amp == 8 else (False,):
+                    code = code_of(lambda: sv.contract(at, 2 * at, 3 * at, n1, n2, e, "{dtype}", fp32=fp32))
+                    assert code == sv.SV_OK, (n1, n2, e, fp32)
+    """)
