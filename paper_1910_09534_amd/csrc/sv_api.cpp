@@ -134,6 +134,7 @@ int set_err(sv_state* h, int code, const std::string& msg)
 
 int fail_dev(sv_state* h, const char* what, hipError_t e, int code = SV_EDEVICE)
 {
+    (void)hipGetLastError();     // told here: the thread's next launch, of another handle, does not fail for it
     std::string m = std::string(what) + ": " + hipGetErrorString(e);
     if (h) {
         h->poisoned = true;

@@ -99,6 +99,7 @@ thread_local std::string g_batch_error;
 
 int berr(sv_batch_s* b, int code, const std::string& m)
 {
+    if (code == SV_EDEVICE) (void)hipGetLastError();     // told here, not by the thread's next launch
     if (b) b->err = m;
     else g_batch_error = m;
     return code;

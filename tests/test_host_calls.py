@@ -106,3 +106,23 @@ def test_contractions_at_every_size(fake_hip, dtype):
                     code = code_of(lambda: sv.contract(at, 2 * at, 3 * at, n1, n2, e, "{dtype}", fp32=fp32))
                     assert code == sv.SV_OK, (n1, n2, e, fp32)
     """)
+
+
+@pytest.mark.parametrize("api", ["hipMemcpyAsync", "hipEventRecord"])
+def test_failed_call_leaves_other_handles(fake_hip, api):
+    """A runtime call that fails is told by the call that made it: its handle
+    is unusable from then on, another one's next launch does not fail for it."""
+    run(fake_hip, f"""
+    a, b, c = (sv.create_state(12, 0, "c64") for _ in range(3))
+    batch = sv.batch_prepare([a], graph=False)
+    if "{api}" == "hipMemcpyAsync":
+        F.fake_fail(b"{api}", 1)
+        assert code_of(sv.reduce_slices_noalloc, a, np.arange(4, dtype=np.uint64)) == sv.SV_EDEVICE
+        assert code_of(sv.sync_state, a) == sv.SV_ESTATE
+    else:
+        F.fake_fail(b"{api}", 1)
+        assert code_of(sv.batch_launch, batch) == sv.SV_EDEVICE
+    sv.apply_diag(b, [0], np.ones(2), "c64")
+    assert code_of(sv.sync_state, b) == sv.SV_OK
+    sv.reduce_slices(c, np.arange(4, dtype=np.uint64))
+    """)
