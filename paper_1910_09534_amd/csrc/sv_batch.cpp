@@ -522,21 +522,24 @@ int sv_batch_launch(sv_batch b)
     // variant, which writes |0...0> only where a plain sweep needs it
     bool reset = true;
     for (sv_state* h : b->states) reset = reset && h->e0_pending && h->sparse_start;
-    // order after everything already queued on the states' own streams
     for (size_t i = 0; i < b->states.size(); ++i) {
-        sv_state* h = b->states[i];
+        const sv_state* h = b->states[i];
         if (h->poisoned) return SV_ESTATE;
         if (!h->ops.empty()) return berr(b, SV_EINVAL, "state has operations queued after the batch was prepared");
         if (h->dev != b->devs[i] || h->order != b->orders[i])
             return berr(b, SV_EINVAL, "state was re-laid out (permute_qubits) after the batch was prepared");
-        // otherwise a deferred reset is written on the state's stream, ahead of the batch
+    }
+    // order after everything already queued on the states' own streams (no
+    // state changes up to the launch: a call that fails before it leaves each
+    // as it was, a deferred reset among them)
+    for (size_t i = 0; i < b->states.size(); ++i) {
+        sv_state* h = b->states[i];
+        // without the reset variant a deferred reset is written on the state's
+        // stream, ahead of the batch
         if (!reset && (h->e0_pending || h->garbage)) {
             const int rc = materialize_e0(h);
             if (rc) return rc;
         }
-        h->e0_pending = false;
-        h->garbage = false;
-        h->support = ~0ull;
         if (hipEventRecord(b->ev_in[i], h->stream) != hipSuccess ||
             hipStreamWaitEvent(b->stream, b->ev_in[i], 0) != hipSuccess)
             return berr(b, SV_EDEVICE, "stream ordering failed");
@@ -550,6 +553,9 @@ int sv_batch_launch(sv_batch b)
     }
     for (size_t i = 0; i < b->states.size(); ++i) {
         sv_state* h = b->states[i];
+        h->e0_pending = false;
+        h->garbage = false;
+        h->support = ~0ull;
         h->amp_bound = (reset ? 1.0 : h->amp_bound) * b->gprod[i];
     }
     if (hipEventRecord(b->ev_done, b->stream) != hipSuccess) return berr(b, SV_EDEVICE, "event record failed");

@@ -4,7 +4,7 @@
 // kept in a log and checked against HIP's documented limits.  Streams and
 // events carry the set of work items ordered before them, so that a buffer
 // freed (or a call returned) while work is still outstanding shows.
-//   fake_fail(api, n)   the n-th call of api from now on (n >= 1) fails
+//   fake_fail(api, n)   the n-th call of api from now on fails (0: none)
 //   fake_fail_always    every call of api fails (on = 1) or none does
 //   fake_log            one line per call, since fake_clear
 //   fake_undone         work items launched and not known to be complete
@@ -119,7 +119,11 @@ const char* fake_log() { return g_log.c_str(); }
 void fake_clear() { g_log.clear(); }
 long fake_undone() { return (long)g_undone.size(); }
 long fake_bad_frees() { return g_bad_frees; }
-void fake_fail(const char* api, int n) { g_fail[api] = n; }
+void fake_fail(const char* api, int n)
+{
+    if (n > 0) g_fail[api] = n;
+    else g_fail.erase(api);
+}
 void fake_fail_always(const char* api, int on)
 {
     if (on) g_fail_always.insert(api);

@@ -126,3 +126,40 @@ def test_failed_call_leaves_other_handles(fake_hip, api):
     assert code_of(sv.sync_state, b) == sv.SV_OK
     sv.reduce_slices(c, np.arange(4, dtype=np.uint64))
     """)
+
+
+BATCH = """
+def batch(graph, sizes=(20, 21, 22, 20, 23, 12)):
+    hs = [sv.create_state(n, 0, "c64") for n in sizes]
+    for h in hs:
+        for q in range(0, 10, 5):
+            sv.apply_fused(h, list(range(q, q + 5)), unitary(5), "c64")
+    b = sv.batch_prepare(hs, graph=graph)
+    for h in hs:
+        sv.sync_state(h)
+    assert F.fake_undone() == 0
+    return hs, b
+"""
+
+
+@pytest.mark.parametrize("what", ["queued", "unusable", "permuted"])
+def test_batch_refused_leaves_the_other_states(fake_hip, what):
+    """A batch that is refused for one of its states leaves the others as they
+    were: a reset that is not yet written stays to be written."""
+    run(fake_hip, BATCH + textwrap.dedent(f"""
+    hs, b = batch(True)
+    if "{what}" == "queued":
+        sv.apply_diag(hs[-1], [0], np.ones(2), "c64")
+    elif "{what}" == "unusable":
+        F.fake_fail(b"hipLaunchKernel", 1)
+        assert code_of(sv.reduce_slices, hs[-1], np.arange(4, dtype=np.uint64)) == sv.SV_EDEVICE
+    else:
+        sv.permute_qubits(hs[-1], list(range(12))[::-1])
+    for h in hs[:-1]:
+        sv.reset(h)
+    assert code_of(sv.batch_launch, b) == (sv.SV_ESTATE if "{what}" == "unusable" else sv.SV_EINVAL)
+    for h in hs[:-1]:
+        F.fake_clear()
+        sv.reduce_slices(h, np.arange(4, dtype=np.uint64))
+        assert any("k_fill" in x for x in log())
+    """))
