@@ -105,12 +105,18 @@ int berr(sv_batch_s* b, int code, const std::string& m)
     return code;
 }
 
-void free_batch(sv_batch_s* b)
+// waits for everything launched on the batch's streams
+void drain(sv_batch_s* b)
 {
-    if (!b) return;
     if (b->stream) (void)hipStreamSynchronize(b->stream);
     for (int l = 1; l < kLanes; ++l)
         if (b->lane[l]) (void)hipStreamSynchronize(b->lane[l]);
+}
+
+void free_batch(sv_batch_s* b)
+{
+    if (!b) return;
+    drain(b);
     for (int v = 0; v < 2; ++v)
         for (int l = 0; l < kLanes; ++l) {
             if (b->exec[v][l]) (void)hipGraphExecDestroy(b->exec[v][l]);
@@ -209,7 +215,7 @@ hipError_t capture_lane(sv_batch_s* b, const std::vector<Launch>& launches, cons
 }
 
 // the lanes' graphs side by side, between the work before and after them on
-// the batch's stream
+// the batch's stream (after an error some of them may run: drain)
 hipError_t launch_lanes(sv_batch_s* b, const hipGraphExec_t* exec)
 {
     bool fork = false;
@@ -547,7 +553,13 @@ int sv_batch_launch(sv_batch b)
     b->last_reset = reset;
     hipError_t e = b->captured ? launch_lanes(b, b->exec[reset ? 1 : 0])
                                : enqueue_all(b, reset ? b->launches_reset : b->launches);
+    if (e == hipSuccess) e = hipEventRecord(b->ev_done, b->stream);
+    for (sv_state* h : b->states)
+        if (e == hipSuccess) e = hipStreamWaitEvent(h->stream, b->ev_done, 0);
     if (e != hipSuccess) {
+        // what was launched may still write the states, and their streams do
+        // not wait for it: it ends here
+        drain(b);
         for (sv_state* h : b->states) { h->poisoned = true; h->err = "batch launch failed"; }
         return berr(b, SV_EDEVICE, std::string("batch launch failed: ") + hipGetErrorString(e));
     }
@@ -558,10 +570,6 @@ int sv_batch_launch(sv_batch b)
         h->support = ~0ull;
         h->amp_bound = (reset ? 1.0 : h->amp_bound) * b->gprod[i];
     }
-    if (hipEventRecord(b->ev_done, b->stream) != hipSuccess) return berr(b, SV_EDEVICE, "event record failed");
-    for (sv_state* h : b->states)
-        if (hipStreamWaitEvent(h->stream, b->ev_done, 0) != hipSuccess)
-            return berr(b, SV_EDEVICE, "stream ordering failed");
     return SV_OK;
 }
 

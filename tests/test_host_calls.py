@@ -142,6 +142,44 @@ def batch(graph, sizes=(20, 21, 22, 20, 23, 12)):
 """
 
 
+@pytest.mark.parametrize("graph", [True, False])
+@pytest.mark.parametrize("api", ["hipGraphLaunch", "hipLaunchKernel", "hipEventRecord", "hipStreamWaitEvent"])
+def test_batch_launch_that_fails(fake_hip, api, graph):
+    """However far a batch launch gets before a runtime call fails, nothing of
+    it runs on when it returns (the caller may free the states), and no state
+    is half of one thing: usable as it was before, or refused."""
+    run(fake_hip, BATCH + textwrap.dedent(f"""
+    bits = np.arange(4, dtype=np.uint64)
+    failed = 0
+    for nth in range(1, 40):
+        hs, b = batch({graph})
+        for h in hs:
+            sv.reset(h)
+        F.fake_fail(b"{api}", nth)
+        F.fake_clear()
+        code = code_of(sv.batch_launch, b)
+        ran = any(x.startswith(("graph", "launch")) for x in log())
+        F.fake_fail(b"{api}", 0)                                  # (not reached: off)
+        if code == sv.SV_OK:
+            for h in hs:
+                sv.destroy_state(h)
+            sv.batch_destroy(b)
+            continue
+        failed += 1
+        assert F.fake_undone() == 0, nth
+        for h in hs:
+            if ran:
+                assert code_of(sv.reduce_slices, h, bits) == sv.SV_ESTATE, nth
+            else:
+                F.fake_clear()
+                if code_of(sv.reduce_slices, h, bits) == sv.SV_OK:
+                    assert any("k_fill" in x for x in log()), nth     # the reset is still to be written
+            sv.destroy_state(h)
+        sv.batch_destroy(b)
+    assert failed or "{api}" == ("hipLaunchKernel" if {graph} else "hipGraphLaunch")
+    """))
+
+
 @pytest.mark.parametrize("what", ["queued", "unusable", "permuted"])
 def test_batch_refused_leaves_the_other_states(fake_hip, what):
     """A batch that is refused for one of its states leaves the others as they
