@@ -1409,10 +1409,12 @@ int reduce_resident(sv_state* h, const double* T, int64_t count, const uint64_t*
         if (count > 0) std::memcpy(hb, bits, (size_t)count * 8);
         bsrc = hb;
     }
-    if (stats && !wb && !h->ticket_ready) {
+    // the handle's own ticket once (k_reduce leaves it at zero); that of a
+    // shared work area on every call: one that failed may have left it counting
+    if (stats && (wb || !h->ticket_ready)) {
         const double zero[8] = {};
         TRY(h, launch_upload(st, w.small, zero, sizeof(zero)));
-        h->ticket_ready = true;
+        if (!wb) h->ticket_ready = true;
     }
     TRY(h, launch_reduce(st, h->dev, h->dtype, h->L, ns, l2p, count, bsrc, T ? w.tcol : nullptr,
                          (const int*)w.rowmap, adst, (double)h->n, (double*)w.part, norm_blocks,

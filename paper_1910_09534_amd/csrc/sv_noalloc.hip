@@ -105,5 +105,8 @@ extern "C" int reduce_slices_noalloc(sv_handle h, const void* trailing_c128, int
     char* b = (char*)base;
     const sv::WorkBufs wb{b + kOffBits, b + kOffAcc, b + kOffPart, b + kOffTcol, b + kOffRowmap,
                           b + kOffSmall, b + kOffArena, kArenaBytes};
-    return sv::reduce_with(h, trailing_c128, count, bitstrings, out_c128, stats, &wb);
+    const int rc = sv::reduce_with(h, trailing_c128, count, bitstrings, out_c128, stats, &wb);
+    // what a failed call launched still uses the array: not the next caller's yet
+    if (rc != SV_OK) (void)hipStreamSynchronize(h->stream);
+    return rc;
 }

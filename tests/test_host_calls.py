@@ -201,3 +201,24 @@ def test_batch_refused_leaves_the_other_states(fake_hip, what):
         sv.reduce_slices(h, np.arange(4, dtype=np.uint64))
         assert any("k_fill" in x for x in log())
     """))
+
+
+@pytest.mark.parametrize("nth", [1, 2, 3])
+def test_noalloc_call_after_one_that_failed(fake_hip, nth):
+    """The shared work array of reduce_slices_noalloc keeps nothing of a call
+    that failed: it is idle when that call returns, and the next call, of
+    another handle, starts with its ticket at zero."""
+    run(fake_hip, f"""
+    bits = np.arange(4, dtype=np.uint64)
+    a, b = (sv.create_state(12, 0, "c64") for _ in range(2))
+    for h in (a, b):
+        sv.sync_state(h)
+    F.fake_fail(b"hipMemcpyAsync", {nth})
+    assert code_of(sv.reduce_slices_noalloc, a, bits) == sv.SV_EDEVICE
+    assert F.fake_undone() == 0
+    F.fake_clear()
+    for _ in range(2):
+        assert code_of(sv.reduce_slices_noalloc, b, bits) == sv.SV_OK
+    assert "stale ticket" not in log()
+    assert code_of(sv.reduce_slices, b, bits) == sv.SV_OK
+    """)
