@@ -1352,7 +1352,8 @@ void slice_columns(const sv_state* h, const double* T, std::vector<int>& rowmap,
 
 // Resident states: the queue, then one launch that reads the bitstrings from
 // pinned memory and writes amplitudes and sums there (up to
-// kPinnedBitstrings; larger calls, and those that may not allocate, copy).
+// kPinnedBitstrings; larger calls, those that may not allocate and those that
+// get no pinned memory copy).
 constexpr int64_t kPinnedBitstrings = 1 << 17;
 
 int reduce_resident(sv_state* h, const double* T, int64_t count, const uint64_t* bits, void* out, double* stats,
@@ -1360,7 +1361,7 @@ int reduce_resident(sv_state* h, const double* T, int64_t count, const uint64_t*
 {
     const int ns = 1 << h->s;
     const size_t cnt = (size_t)std::max<int64_t>(count, 1);
-    const bool pinned = !wb && count <= kPinnedBitstrings;
+    bool pinned = !wb && count <= kPinnedBitstrings;
     hipStream_t st = h->stream;
     int rc;
     WorkBufs w;
@@ -1368,15 +1369,16 @@ int reduce_resident(sv_state* h, const double* T, int64_t count, const uint64_t*
         w = *wb;
     } else {
         if ((rc = ensure_dev(h, &h->d_part, &h->d_part_cap, kPartDoubles * sizeof(double)))) return rc;
-        if (!pinned) {
-            if ((rc = ensure_dev(h, &h->d_bits, &h->d_bits_cap, cnt * 8))) return rc;
-            if ((rc = ensure_dev(h, &h->d_acc, &h->d_acc_cap, cnt * 16))) return rc;
-        } else if (h->h_red_cap < 64 + cnt * 24) {
+        if (pinned && h->h_red_cap < 64 + cnt * 24) {
             // (idle: every reduction waits for its results)
             if (h->h_red) pool_free(h->h_red, h->h_red_cap, true);
             h->h_red_cap = 0;
             h->h_red = pool_alloc(64 + cnt * 24, true, &h->h_red_cap);
-            if (!h->h_red) return set_err(h, SV_ENOMEM, "pinned staging allocation failed");
+            pinned = h->h_red != nullptr;                // (none to be had: by copies)
+        }
+        if (!pinned) {
+            if ((rc = ensure_dev(h, &h->d_bits, &h->d_bits_cap, cnt * 8))) return rc;
+            if ((rc = ensure_dev(h, &h->d_acc, &h->d_acc_cap, cnt * 16))) return rc;
         }
         if (T) {
             if ((rc = ensure_dev(h, &h->d_tcol, &h->d_tcol_cap, (size_t)ns * ns * 16))) return rc;

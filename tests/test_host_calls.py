@@ -222,3 +222,22 @@ def test_noalloc_call_after_one_that_failed(fake_hip, nth):
     assert "stale ticket" not in log()
     assert code_of(sv.reduce_slices, b, bits) == sv.SV_OK
     """)
+
+
+@pytest.mark.parametrize("count", [0, 4, 1 << 12])
+def test_reduction_without_pinned_memory(fake_hip, count):
+    """No pinned memory to be had: a resident state's reduction copies."""
+    run(fake_hip, f"""
+    bits = np.arange({count}, dtype=np.uint64)
+    h = sv.create_state(12, 0, "c64")
+    F.fake_fail_always(b"hipHostMalloc", 1)
+    for _ in range(2):
+        assert code_of(sv.reduce_slices, h, bits) == sv.SV_OK
+        assert code_of(sv.gather_amplitudes, h, bits) == sv.SV_OK
+    F.fake_fail_always(b"hipHostMalloc", 0)
+    F.fake_clear()
+    assert code_of(sv.reduce_slices, h, bits) == sv.SV_OK
+    assert not any(x.startswith("copy") for x in log())       # pinned again
+    sv.destroy_state(h)
+    assert F.fake_bad_frees() == 0
+    """)
