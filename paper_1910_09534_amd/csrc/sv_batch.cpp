@@ -501,13 +501,16 @@ int sv_batch_prepare(int count, sv_handle* handles, int flags, void* hip_stream,
         }
         for (const sv_state* h : b->states)
             if (h->n >= kWideQubits) b->lanes = kLanes;
-        const std::vector<int> lane = deal_lanes(b);
         b->lane[0] = b->stream;
         e = hipEventCreateWithFlags(&b->ev_fork, hipEventDisableTiming);
-        for (int l = 1; l < b->lanes && e == hipSuccess; ++l) {
-            e = hipStreamCreateWithFlags(&b->lane[l], hipStreamNonBlocking);
-            if (e == hipSuccess) e = hipEventCreateWithFlags(&b->ev_lane[l], hipEventDisableTiming);
-        }
+        // (as many lanes as there are streams to be had)
+        for (int l = 1; l < b->lanes && e == hipSuccess; ++l)
+            if (hipStreamCreateWithFlags(&b->lane[l], hipStreamNonBlocking) != hipSuccess ||
+                hipEventCreateWithFlags(&b->ev_lane[l], hipEventDisableTiming) != hipSuccess) {
+                (void)hipGetLastError();
+                b->lanes = l;
+            }
+        const std::vector<int> lane = deal_lanes(b);
         for (int v = 0; v < 2; ++v)
             for (int l = 0; l < b->lanes && e == hipSuccess; ++l)
                 e = capture_lane(b, v ? b->launches_reset : b->launches, lane, l, &b->graph[v][l], &b->exec[v][l]);

@@ -241,3 +241,28 @@ def test_reduction_without_pinned_memory(fake_hip, count):
     sv.destroy_state(h)
     assert F.fake_bad_frees() == 0
     """)
+
+
+@pytest.mark.parametrize("left", [0, 1, 3])
+def test_batch_with_few_streams(fake_hip, left):
+    """A batch's graphs take as many streams as there are: each state's
+    launches are in one of them, and the batch runs."""
+    run(fake_hip, BATCH + textwrap.dedent(f"""
+    hs, b = batch(True)
+    F.fake_clear()
+    sv.batch_launch(b)
+    graphs = sum(x.startswith("graph") for x in log())
+    assert graphs == 6
+    hs = [sv.create_state(n, 0, "c64") for n in (20, 21, 22, 20, 23, 12)]
+    for h in hs:
+        sv.apply_fused(h, [1, 2, 3, 4, 5], unitary(5), "c64")
+    F.fake_clear()
+    F.fake_fail(b"hipStreamCreateWithFlags", 2 + {left})       # the batch's own comes first
+    b = sv.batch_prepare(hs, graph=True)
+    passes = [x for x in log() if x.startswith("launch") and ("k_split" in x or "k_stage" in x)]
+    F.fake_clear()
+    sv.batch_launch(b)
+    assert sum(x.startswith("graph") for x in log()) == 1 + {left}
+    assert len(passes) == 2 * 6                                # both variants, one pass a state
+    sv.batch_destroy(b)
+    """))
