@@ -1041,6 +1041,17 @@ int measure_bound(sv_state* h, const WorkBufs* wb)
     return SV_OK;
 }
 
+// the queue is applied: the amplitude bound advances over it
+void queue_applied(sv_state* h)
+{
+    for (Op& op : h->ops) {
+        size_op(op, h->arena.data(), h->amp);
+        h->amp_bound *= op.growth;
+    }
+    h->ops.clear();
+    h->arena.clear();
+}
+
 int flush(sv_state* h, double* norm_out = nullptr, int* norm_blocks = nullptr, const WorkBufs* wb = nullptr)
 {
     if (norm_blocks) *norm_blocks = 0;
@@ -1062,13 +1073,7 @@ int flush(sv_state* h, double* norm_out = nullptr, int* norm_blocks = nullptr, c
         rc = tier_pass(h, true, [](int, void*) { return SV_OK; });
         if (rc) return rc;
     }
-    // the queue is applied: the bound advances over it
-    for (Op& op : h->ops) {
-        size_op(op, h->arena.data(), h->amp);
-        h->amp_bound *= op.growth;
-    }
-    h->ops.clear();
-    h->arena.clear();
+    queue_applied(h);
     if (h->timing) return collect_timing(h);
     return SV_OK;
 }
@@ -1493,8 +1498,7 @@ int do_reduce(sv_state* h, const void* trailing, int64_t count, const uint64_t* 
     }
     rc = tier_pass(h, pending, visit);
     if (rc) return rc;
-    h->ops.clear();
-    h->arena.clear();
+    queue_applied(h);
     if (h->timing) rc = collect_timing(h);
     if (rc) return rc;
     if (count > 0)

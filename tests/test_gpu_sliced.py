@@ -323,3 +323,28 @@ def test_pinned_tier_runs_of_files(n, S, dtype):
     finally:
         for st in sts:
             st.close()
+
+
+@pytest.mark.parametrize("n", [16, 22])
+def test_blocks_after_a_reduction_of_a_grown_state(n):
+    """A gate that raises the norm, applied by a reduction of the tier, then
+    unitary blocks: the split-fp16 passes' scale leaves room for the larger
+    amplitudes (a whole small tier, and slice by slice)."""
+    _gpu()
+    rng = np.random.default_rng(n)
+    st = sv.State(n, (1 << (n - 1)) | (1 << (n - 2)), "c64", tier=True)
+    psi = orc.zero_state(n)
+    try:
+        ops = [([0, 1, 2, 3, 4], W.random_unitary(32, rng)), ([5], np.diag([3e4, 1.0])),
+               ([2, 5, 6, 7, 8], W.random_unitary(32, rng)), ([6, 7, 9, 10, 11], W.random_unitary(32, rng))]
+        bits = W.bitstrings(n, 4096, seed=n)
+        for i, (qs, m) in enumerate(ops):
+            st.fused(qs, m)
+            orc.apply_dense(psi, qs, m.astype(np.complex128))
+            if i == 1:
+                st.reduce(bits)
+        got = st.gather(bits & np.uint64((1 << 12) - 1))
+        assert sv.stage_forms(st.h)["split"] > 0
+    finally:
+        st.close()
+    assert orc.rel_l2(got, orc.gather(psi, bits & np.uint64((1 << 12) - 1))) <= TOL["c64"]

@@ -266,3 +266,21 @@ def test_batch_with_few_streams(fake_hip, left):
     assert len(passes) == 2 * 6                                # both variants, one pass a state
     sv.batch_destroy(b)
     """))
+
+
+@pytest.mark.parametrize("where", ["resident", "whole", "slices", "pageable"])
+def test_amplitude_bound_follows_reductions(fake_hip, where):
+    """A reduction applies the queue, so the bound on the amplitudes, from
+    which the split-fp16 passes take their scale, grows with it."""
+    run(fake_hip, f"""
+    n = {{"resident": 12, "whole": 12, "slices": 22, "pageable": 12}}["{where}"]
+    tier = "{where}" != "resident"
+    h = sv.create_state(n, 5 if tier else 0, "c64", tier=tier, pageable="{where}" == "pageable")
+    sv.apply_diag(h, [1], np.array([1000.0, 1.0]), "c64")
+    sv.reduce_slices(h, np.arange(4, dtype=np.uint64))
+    sv.apply_diag(h, [1], np.array([1.0, 20.0]), "c64")
+    sv.gather_amplitudes(h, np.arange(4, dtype=np.uint64))
+    assert abs(sv.stage_forms(h)["amp_bound"] / 20000.0 - 1) < 1e-3
+    sv.reset(h)
+    assert sv.stage_forms(h)["amp_bound"] == 1.0
+    """)
