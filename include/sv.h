@@ -273,7 +273,8 @@ enum {
                               cores (default 4); 0 or > 6: never */
     SV_OPT_FOLD_DIAG = 3,  /* 1 (default): fold a diagonal op into the preceding dense sweep */
     SV_OPT_SLOTS = 4,      /* tier: number of device slice slots (>= 2) */
-    SV_OPT_STAGE = 5,      /* widest LDS tile (9..14 positions, default 13) for running a
+    SV_OPT_STAGE = 5,      /* widest LDS tile (9..14 positions, default 13, 14 for a lone
+                              5-qubit block on 2^28 amplitudes or more) for running a
                               run of consecutive 4/5-qubit blocks in one pass over HBM
                               (complex64: 14 = one workgroup per CU, 1024 lanes in the split
                               form and 512 in the fp32 form, holding the

@@ -343,7 +343,7 @@ int run_ops(sv_state* h, hipStream_t st, void** psi, void* alt, int nloc, uint64
                 TRY(h, launch_stage(st, *psi, nloc, cnt, ks, pp, mm, stage_t, from_e0,
                                     last ? norm_out : nullptr, last ? norm_blocks : nullptr, &tused,
                                     track ? h->support : ~0ull, track && h->garbage, &pmask, &visited,
-                                    split_exp, h->dtype));
+                                    split_exp, h->dtype, h->lone_t));
                 h->stage_forms[split_exp != kNoSplit ? 0 : 1] += 1;
                 h->e0_pending = false;
                 if (track) {
@@ -2045,7 +2045,7 @@ int sv_set_option(sv_handle h, int option, int64_t value)
         case SV_OPT_STAGE:
             if (value != 0 && (value < 9 || value > 14))
                 return set_err(h, SV_EINVAL, "SV_OPT_STAGE: 0 or 9..14 positions");
-            h->stage_t = (int)value;
+            h->stage_t = h->lone_t = (int)value;
             return SV_OK;
         case SV_OPT_FAIL_IO: h->fail_io_at = value; return SV_OK;
         case SV_OPT_SPARSE_START: h->sparse_start = value != 0; return SV_OK;

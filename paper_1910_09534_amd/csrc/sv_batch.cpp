@@ -46,6 +46,7 @@ struct Launch {
     bool from_e0 = false, garbage = false;
     uint64_t support = ~0ull;
     int split_exp = kNoSplit;                 // staged: split-fp16 tile scale exponent
+    int lone_t = 0;                           // staged: tile limit of a lone 5-qubit block on a large state
     std::vector<int> who;                     // the states it works on
 };
 
@@ -150,7 +151,7 @@ hipError_t enqueue_one(sv_batch_s* b, const Launch& L, hipStream_t st)
     for (int c = 0; c < L.cnt; ++c) pp[c] = L.spos[c];
     int t = 0;
     return launch_stage(st, L.psi, L.nloc, L.cnt, L.ks, pp, L.smat, L.t_max, L.from_e0, nullptr, nullptr, &t,
-                        L.support, L.garbage, nullptr, nullptr, L.split_exp);
+                        L.support, L.garbage, nullptr, nullptr, L.split_exp, 0, L.lone_t);
 }
 
 hipError_t enqueue_all(sv_batch_s* b, const std::vector<Launch>& launches)
@@ -377,6 +378,7 @@ int sv_batch_prepare(int count, sv_handle* handles, int flags, void* hip_stream,
                 L.cnt = w.cnt;
                 L.who = {i};
                 L.t_max = h->stage_t;
+                L.lone_t = h->lone_t;
                 bool unit = h->split;
                 double bmax = rs_bound[i];
                 for (int c = 0; c < w.cnt; ++c) {

@@ -118,7 +118,8 @@ inline bool dense_uses_mfma(int k, int nloc, int mfma_min_k)
 // stay zero, and the tile is widened with support positions only.  garbage: the memory outside the support's reach is not zero,
 // so tile amplitudes with a bit on a tile position outside the support are
 // taken as zero instead of read.  *tile_mask_out: the tile's positions;
-// *amps_out: amplitudes visited.
+// *amps_out: amplitudes visited.  lone_t: tile limit of a pass of one 5-qubit
+// block on a large state (0: t_max; split-fp16 form).
 // dtype 0: complex64 (fp32 or split-fp16 form); 1: complex128 (FP64 form,
 // eight waves per CU, tiles of 9..13 positions).
 int stage_lds_bytes(int t, int nops, const int* ks, int dtype = 0);
@@ -140,17 +141,23 @@ hipError_t launch_stage(hipStream_t st, void* psi, int nloc, int nops, const int
                         const void* const* mats, int t_max, bool from_e0, double* norm_out, int* norm_blocks,
                         int* t_out, uint64_t support = ~0ull, bool garbage = false,
                         uint64_t* tile_mask_out = nullptr, uint64_t* amps_out = nullptr,
-                        int split_exp = kNoSplit, int dtype = 0);
+                        int split_exp = kNoSplit, int dtype = 0, int lone_t = 0);
 // The split-fp16 form of a staged pass (sv_split.hip), called by launch_stage
 // with the tile chosen: positions P[0..t), the tiles' mask over the other
 // positions, newmask = the tile positions whose elements are zero but may
-// hold older values.  split_prepare: LDS attribute of a tile width's kernels.
+// hold older values, park: every tile through LDS on both sides.
+// split_prepare: LDS attribute of a tile width's kernels.
 hipError_t launch_split(hipStream_t st, void* psi, int t, const int* P, int nops, const int* ks,
                         const int* const* pos, const void* const* mats, uint64_t tiles, uint64_t tmask,
-                        uint64_t newmask, bool from_e0, double* norm_out, int* norm_blocks, int split_exp);
+                        uint64_t newmask, bool from_e0, double* norm_out, int* norm_blocks, int split_exp, bool park);
 hipError_t split_prepare(int t, int lds);
-// Tile limit of a pass of one block on 2^bits amplitudes (at most t_max).
-int split_lone_width(int k, const int* pos, int bits, int t_max);
+// Tile limit of a pass of one block on 2^bits amplitudes (at most t_max; 5 qubits
+// on a large state: wide_max) and whether its tiles are parked in LDS on both sides.
+struct SplitLone {
+    int t_max;
+    bool park;
+};
+SplitLone split_lone(int k, const int* pos, int bits, int t_max, int wide_max);
 // The same for complex128 (sv_stage64.hip).
 hipError_t launch_stage64(hipStream_t st, void* psi, int t, const int* P, int nops, const int* ks,
                           const int* const* pos, const void* const* mats, uint64_t tiles, uint64_t tmask,

@@ -27,7 +27,7 @@
 // its results straight to HBM: a run of n blocks makes n - 1 trips through
 // LDS instead of n + 1, and a lone block none.  Where a block's own layout is a
 // poor order for the memory, a parking step takes its side of the pass
-// (linear_layout, split_lone_width).
+// (linear_layout, split_lone).
 //
 // The two amplitudes of an access are two groups when position 0 is no
 // target of the block, and two matrix columns (bit b0) when it is.
@@ -618,27 +618,38 @@ bool split_narrow(int k, const int* pos)
     return low == 14;
 }
 
-// amplitudes (as bits) from which a lone block's pass is parked or narrowed
-constexpr int kLoneBits = 27, kLoneNarrowBits = 24;
+// amplitudes (as bits) from which a lone block's pass is parked, narrowed, or
+// wider than the default limit
+constexpr int kLoneBits = 27, kLoneNarrowBits = 24, kLoneWideBits = 28;
 
 }  // namespace
 
-// Tile width of a pass of one block.  What it costs is the order in which it
-// touches memory: on the block's own layout the waves of a wide tile hold
-// accesses whose addresses agree in the bits that choose the memory channel.
-// Parked on both sides, a 14-position tile is read and written as one stretch
-// of 128 KiB; without that width, short tiles spread over more workgroups do
-// better.  Mean over 12 sets of targets (direct, 13 positions -> direct, 12 ->
-// parked, 13 -> parked, 14): 2^30 amplitudes, 5 qubits 3,482 -> 3,355 -> 3,352 ->
-// 3,178 us, 4 qubits 3,472 -> 3,447 -> 3,332 -> 3,176; 2^25, 5 qubits 124 -> 119 ->
-// 121 -> 122, 4 qubits 116 -> 110 -> 111 -> 114; 2^22 32.1 and 25.4 direct
-// against 35 and 27 parked.
-int split_lone_width(int k, const int* pos, int bits, int t_max)
+// A pass of one block.  What it costs is the order in which it touches memory:
+// on the block's own layout the waves of a wide tile hold accesses whose
+// addresses agree in the bits that choose the memory channel.  Parked on both
+// sides, a 14-position tile is read and written as one stretch of 128 KiB;
+// without that width, short tiles spread over more workgroups do better.  Mean
+// over 12 sets of targets (direct, 13 positions -> direct, 12 -> parked, 13 ->
+// parked, 14): 2^30 amplitudes, 5 qubits 3,482 -> 3,355 -> 3,352 -> 3,178 us, 4
+// qubits 3,472 -> 3,447 -> 3,332 -> 3,176; 2^25, 5 qubits 124 -> 119 -> 121 ->
+// 122, 4 qubits 116 -> 110 -> 111 -> 114; 2^22 32.1 and 25.4 direct against 35
+// and 27 parked.
+//
+// Where the caller left the tile limit at its default of 13, a block of 5 qubits
+// on a large state takes 14 positions all the same: direct, 12, is as fast as
+// parked, 13, on average, but up to a fifth slower for single sets of targets.
+// 32 sets each, mean and slowest set against parked 13-position tiles with the
+// block on LDS (direct, 12 -> parked, 14): 2^27 437 us: 417, 0.93 -> 428, 0.94;
+// 2^28 853: 859, 0.83 -> 831, 0.91; 2^29 1,758: 1,683, 0.85 -> 1,637, 0.91; 2^30
+// 3,465: 3,435, 0.83 -> 3,267, 0.93.  4 qubits (parked, 13 -> parked, 14): 2^29
+// 1,668: 1,612, 0.92 -> 1,591, 0.89; 2^30 3,449: 3,317, 1.00 -> 3,239, 0.95.
+SplitLone split_lone(int k, const int* pos, int bits, int t_max, int wide_max)
 {
-    if (bits < kLoneNarrowBits || split_narrow(k, pos)) return t_max;
-    if (bits >= kLoneBits && t_max >= 14) return 14;
-    if (bits >= kLoneBits && k == 4 && t_max >= 13) return 13;
-    return t_max < 12 ? t_max : 12;
+    if (bits < kLoneNarrowBits || split_narrow(k, pos)) return {t_max, false};
+    if (bits >= kLoneBits && t_max >= 14) return {14, true};
+    if (bits >= kLoneWideBits && k == 5 && wide_max >= 14) return {14, true};
+    if (bits >= kLoneBits && k == 4 && t_max >= 13) return {13, true};
+    return {t_max < 12 ? t_max : 12, false};
 }
 
 hipError_t split_prepare(int t, int lds)
@@ -654,13 +665,11 @@ hipError_t split_prepare(int t, int lds)
 
 hipError_t launch_split(hipStream_t st, void* psi, int t, const int* P, int nops, const int* ks,
                         const int* const* pos, const void* const* mats, uint64_t tiles, uint64_t tmask,
-                        uint64_t newmask, bool from_e0, double* norm_out, int* norm_blocks, int split_exp)
+                        uint64_t newmask, bool from_e0, double* norm_out, int* norm_blocks, int split_exp, bool park)
 {
     if (t < 9 || t > 14 || nops < 1 || nops > kSplitMaxOps - 2) return hipErrorInvalidValue;
     // sides that go through a parking step
-    const bool wide = std::ldexp((double)tiles, t) >= std::ldexp(1.0, kLoneBits);
-    const bool lone = nops == 1 && wide && (t == 14 || (t == 13 && ks[0] == 4));
-    bool in = lone || split_narrow(ks[0], pos[0]), out = lone || split_narrow(ks[nops - 1], pos[nops - 1]);
+    bool in = park || split_narrow(ks[0], pos[0]), out = park || split_narrow(ks[nops - 1], pos[nops - 1]);
     {
         int need = (8 << t) + (nops + 2) * 256;
         for (int o = 0; o < nops; ++o) need += 8 << (2 * ks[o]);

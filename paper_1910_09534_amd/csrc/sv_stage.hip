@@ -24,6 +24,7 @@
 // for stores.  Re M and Im M of every block are staged in LDS once per
 // workgroup.  Every workgroup runs the same number of tile iterations, so
 // the barriers are reached uniformly.
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 
@@ -522,12 +523,17 @@ uint64_t stage_visits(int nloc, int nops, const int* ks, const int* const* pos, 
 hipError_t launch_stage(hipStream_t st, void* psi, int nloc, int nops, const int* ks, const int* const* pos,
                         const void* const* mats, int t_max, bool from_e0, double* norm_out, int* norm_blocks,
                         int* t_out, uint64_t support, bool garbage, uint64_t* tile_mask_out,
-                        uint64_t* amps_out, int split_exp, int dtype)
+                        uint64_t* amps_out, int split_exp, int dtype, int lone_t)
 {
     int P[64];
+    bool park = false;
     if (nops == 1 && split_exp != kNoSplit && ks[0] >= 4 && ks[0] <= 5) {
         const uint64_t seen = support & (nloc >= 64 ? ~0ull : (1ull << nloc) - 1);
-        t_max = split_lone_width(ks[0], pos[0], __builtin_popcountll(seen), t_max);
+        const int dev_t = stage_max_t(dtype);
+        const SplitLone lone = split_lone(ks[0], pos[0], __builtin_popcountll(seen), std::min(t_max, dev_t),
+                                          std::min(lone_t ? lone_t : t_max, dev_t));
+        t_max = lone.t_max;
+        park = lone.park;
     }
     const int t = stage_positions(nloc, nops, ks, pos, t_max, support, P, dtype);
     if (t < 0) return hipErrorInvalidValue;
@@ -555,7 +561,7 @@ hipError_t launch_stage(hipStream_t st, void* psi, int nloc, int nops, const int
         hipError_t e = stage_prepare();
         if (e != hipSuccess) return e;
         e = launch_split(st, psi, t, P, nops, ks, pos, mats, a.tiles, a.tmask, newmask, from_e0, norm_out,
-                         norm_blocks, split_exp);
+                         norm_blocks, split_exp, park);
         if (t_out) *t_out = t;
         if (tile_mask_out) *tile_mask_out = pmask;
         if (amps_out) *amps_out = a.tiles << t;

@@ -139,6 +139,7 @@ struct sv_state {
     bool timing = false, fold = true;
     int mfma_min_k = 4;
     int stage_t = 13;            // widest tile of staged multi-block passes (0: off)
+    int lone_t = 14;             // ... of a pass of one 5-qubit block on a large state
     bool split = true;           // staged passes in the split-fp16 form where the amplitude bound allows
     bool e0_pending = false;     // resident state is |0...0> but not yet written (sv_reset)
     // Resident states after sv_reset: every amplitude whose index has a bit

@@ -309,3 +309,33 @@ def test_split_lone_block_large(n, qs, t):
             sv.destroy_state(h)
         outs.append(x)
     assert float(torch.linalg.vector_norm(outs[0] - outs[1])) <= 1e-6
+
+
+@pytest.mark.parametrize("stage", [None, 12, 13, 14])
+@pytest.mark.parametrize("qs", [[0, 5, 12, 19, 26], [8, 3, 22, 13]])
+def test_lone_block_tile_limits(qs, stage):
+    """A lone block on 2^28 amplitudes with the tile limit left at its default
+    and set: the tile's width changes no sum, so every limit gives the bits
+    of the first; bound against a plain fp32 sweep as above."""
+    torch = _torch()
+    n = 28
+    rng = np.random.default_rng(n + len(qs))
+    g = torch.Generator(device="cuda").manual_seed(n)
+    psi = torch.view_as_complex(torch.randn((1 << n, 2), generator=g, device="cuda"))
+    psi /= torch.linalg.vector_norm(psi)
+    u = W.random_unitary(1 << len(qs), rng)
+    outs = []
+    for limit in (stage, 11, 0):
+        x = psi.clone()
+        torch.cuda.synchronize()
+        h = sv.create_state_ext(n, 0, "c64", None, x.data_ptr(), x.numel() * 8, keep=True)
+        try:
+            if limit is not None:
+                sv.set_option(h, sv.SV_OPT_STAGE, limit)
+            sv.apply_fused(h, qs, u, "c64")
+            sv.sync_state(h)
+        finally:
+            sv.destroy_state(h)
+        outs.append(x)
+    assert torch.equal(torch.view_as_real(outs[0]), torch.view_as_real(outs[1]))
+    assert float(torch.linalg.vector_norm(outs[0] - outs[2])) <= 1e-6
