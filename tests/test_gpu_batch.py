@@ -195,3 +195,102 @@ def test_tuned_staged_batch_matches_c128_batch_and_oracle():
         ref = orc.gather(orc.simulate(c), b)
         assert orc.rel_l2(a128, ref) <= 1e-12
         assert orc.rel_l2(a64, ref) <= 1e-4
+
+
+@pytest.mark.parametrize("graph", [True, False])
+def test_batch_c128_blocks_with_and_without_diagonals(graph):
+    """Complex128 blocks of 4 and 5 qubits, plain and with a diagonal folded in,
+    as batched matrix-core sweeps (one unit, several, and many a wave) and as
+    vector sweeps below their size: each state has the bits of the same
+    operations alone, and the oracle's amplitudes.  A block's 2^k-term dot
+    products and a phase: sqrt(2^k) + 2 eps, k = 5 and 4 operations, factor 4."""
+    _gpu()
+    rng = np.random.default_rng(61)
+    states, alone, refs, b = [], [], [], None
+    try:
+        for n in (7, 8, 9, 10, 13, 17, 19):
+            ops = []
+            for k, m in ((4, 0), (5, 3), (4, 2), (5, 0)):
+                ops.append(("fused", [int(q) for q in rng.choice(n, k, replace=False)], W.random_unitary(1 << k, rng)))
+                if m:
+                    ops.append(("diag", [int(q) for q in rng.choice(n, m, replace=False)], W.random_phases(1 << m, rng)))
+            pair = [sv.State(n, 0, "c128") for _ in range(2)]
+            for st in pair:
+                sv.set_option(st.h, sv.SV_OPT_STAGE, 0)              # as in the batch: no staged passes
+                for kind, qs, m in ops:
+                    (sv.apply_fused if kind == "fused" else sv.apply_diag)(st.h, qs, m, "c128")
+            states.append(pair[0])
+            alone.append(pair[1])
+            psi = orc.zero_state(n)
+            for kind, qs, m in ops:
+                orc.apply_dense(psi, qs, m if kind == "fused" else np.diag(m))
+            refs.append(psi)
+        b = sv.batch_prepare([st.h for st in states], graph=graph)
+        sv.batch_launch(b)
+        for st, a, ref in zip(states, alone, refs):
+            bits = np.arange(ref.size, dtype=np.uint64)
+            got = st.gather(bits)
+            assert np.array_equal(got, a.gather(bits)), ref.size
+            assert orc.rel_l2(got, ref) <= 4 * 4 * (np.sqrt(32) + 2) * 2.0 ** -53, ref.size
+    finally:
+        if b is not None:
+            sv.batch_destroy(b)
+        for st in states + alone:
+            st.close()
+
+
+def test_batch_of_wide_and_small_states_side_by_side():
+    """A state of 23 qubits (six graphs side by side) beside small ones that
+    share launches with one another and with it: from a reset, applied again
+    to what is there, and with only some of the states reset."""
+    _gpu()
+    rng = np.random.default_rng(67)
+    U = lambda k: W.random_unitary(1 << k, rng)
+    sizes = (23, 14, 12, 13, 20, 12, 15, 21)
+    plans = []
+    for i, n in enumerate(sizes):
+        pick = lambda k: [int(q) for q in rng.choice(np.arange(4, n), k, replace=False)]
+        ops = [(pick(5), U(5)), (pick(4), U(4))]
+        if i not in (4, 7):                                  # shared vector sweeps of one and two widths
+            ops.insert(1 if i % 2 else 2, (pick(3), U(3)))
+        if i % 3 == 0:
+            ops.append((pick(2), U(2)))
+        plans.append(ops)
+    states, b = [], None
+
+    def applied(psi, ops):
+        for qs, m in ops:
+            orc.apply_dense(psi, qs, m)
+        return psi
+
+    def check(refs, tol):
+        for st, ref, n in zip(states, refs, sizes):
+            bits = W.bitstrings(n, 4096, seed=n)
+            assert orc.rel_l2(st.gather(bits), orc.gather(ref, bits)) <= tol, n
+    try:
+        for n, ops in zip(sizes, plans):
+            st = sv.State(n, 0, "c64")
+            sv.set_option(st.h, sv.SV_OPT_STAGE, 12 if n >= 20 else 9)
+            for qs, m in ops:
+                st.fused(qs, np.asarray(m).astype(np.complex64))
+            states.append(st)
+        b = sv.batch_prepare([st.h for st in states], graph=True)
+        for st in states:
+            sv.reset(st.h)
+        sv.batch_launch(b)
+        refs = [applied(orc.zero_state(n), ops) for n, ops in zip(sizes, plans)]
+        check(refs, 1e-5)
+        sv.batch_launch(b)
+        refs = [applied(ref, ops) for ref, ops in zip(refs, plans)]
+        check(refs, 2e-5)
+        for i in (0, 2, 5):
+            sv.reset(states[i].h)
+            refs[i] = orc.zero_state(sizes[i])
+        sv.batch_launch(b)
+        refs = [applied(ref, ops) for ref, ops in zip(refs, plans)]
+        check(refs, 3e-5)
+    finally:
+        if b is not None:
+            sv.batch_destroy(b)
+        for st in states:
+            st.close()
