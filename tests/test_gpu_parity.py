@@ -914,3 +914,34 @@ def test_diag_large_state(n, dtype):
         got = torch.view_as_complex(psi.double())
         rel = ((got - ref).abs().square().sum() / ref.abs().square().sum()).sqrt().item()
         assert rel <= (2.0 ** -23 if dtype == "c64" else 2.0 ** -52), qs
+
+
+@pytest.mark.parametrize("k", [4, 5])
+def test_dense64_error_against_long_double(k):
+    """A complex128 matrix-core sweep's error against 80-bit sums is no larger
+    than that of adding the products one after the other in double (four real
+    sums of half the length each)."""
+    n = 14
+    rng = np.random.default_rng(70 + k)
+    psi = W.random_state(n, rng)
+    qs = [int(q) for q in rng.choice(n, k, replace=False)]
+    u = W.random_unitary(1 << k, rng)
+    axes = [n - 1 - q for q in reversed(qs)]                    # matrix bit j = qubit qs[j]
+
+    def one_after_the_other(dtype):
+        x = np.moveaxis(psi.astype(dtype).reshape([2] * n), axes, range(k)).reshape(1 << k, -1)
+        y = np.zeros_like(x)
+        for j in range(1 << k):
+            y += u[:, j:j + 1].astype(dtype) * x[j]
+        return np.moveaxis(y.reshape([2] * n), range(k), axes).reshape(-1)
+
+    h, t = state_from_numpy(psi, "c128")
+    try:
+        sv.set_option(h, sv.SV_OPT_STAGE, 0)
+        sv.apply_fused(h, qs, u, "c128")
+        got = read_all(h, n)
+    finally:
+        sv.destroy_state(h)
+    exact = one_after_the_other(np.clongdouble)
+    error = lambda x: float(np.linalg.norm((x - exact).astype(np.complex128)))
+    assert error(got) <= error(one_after_the_other(np.complex128))
