@@ -283,7 +283,7 @@ enum {
                               matrices, a large lone block may take a narrower
                               one; in the split-fp16 form 14 measured fastest
                               for states of 2^23 to 2^30 amplitudes, in the fp32 form
-                              13 at 2^30; complex128: eight waves per CU, tiles
+                              13 at 2^30; complex128: up to eight waves per CU, tiles
                               of at most 13 positions, products on the FP64 matrix
                               cores); 0: one pass per block; other values: SV_EINVAL */
     SV_OPT_FAIL_IO = 6,    /* failure injection for tests: the n-th host-tier transfer
@@ -317,7 +317,8 @@ int sv_set_option(sv_handle h, int option, int64_t value);
  * [1] diagonal sweeps, [2] permute sweeps, [3] amplitudes touched by sweeps
  * (staged passes: the amplitudes they visit),
  * [4] bytes staged host->device, [5] bytes staged device->host, [6] slices
- * skipped because they are known to be zero, [7] blocks applied in staged
+ * skipped because they are known to be zero (not transferred, where a small
+ * pinned tier is swept as a whole), [7] blocks applied in staged
  * multi-block passes.
  * sv_sweep_time -- with SV_OPT_TIMING: total milliseconds and count of timed
  * dense sweeps (HIP events on the handle's stream), reset by the call.

@@ -196,7 +196,9 @@ __global__ __launch_bounds__(kCThreads) void k_contract_mfma(const float2* t1, c
 // us in 64 x 32 with the split after the products, 1,600 in 64 x 64, 1,567 as
 // it is (1.05 PFLOP/s of the 24 MNK issued; the vendor's fp16 product reaches
 // 1.38), the clock down to 1.7 GHz under the load; 15, 15, 10: 25.3 -> 23.6 ->
-// 22.7 ms (1.16).
+// 22.7 ms (1.16).  These are normally distributed values; the tensors of a
+// deferred circuit, three quarters of whose entries are zero, draw less power
+// and take 17.2 ms at 15, 15, 10 (random values with 90 % zeros: the same).
 typedef _Float16 ch8 __attribute__((ext_vector_type(8)));
 typedef _Float16 ch4 __attribute__((ext_vector_type(4)));
 typedef uint32_t cu4 __attribute__((ext_vector_type(4)));
@@ -575,7 +577,8 @@ hipError_t launch_full_tiles(hipStream_t st, const void* t1, const void* t2, voi
 // while the outputs alone leave SIMDs idle and it is long enough to give each
 // wave four steps (2^18 outputs, e = 8: 20.6 us in one part, 22.7 in 16).
 // Measured (n1, n2, e; k_contract_plain -> here): complex128 12, 13, 6
-// 1,874 -> 316 us (54 TFLOP/s of 8 MNK), 12, 13, 10 28,852 -> 3,901 us (70, the
+// 1,874 -> 280 us one after the other, 316-326 on its own (61 and 54 TFLOP/s of
+// 8 MNK), 12, 13, 10 28,852 -> 3,901 us (70, the
 // FP64 matrix product of the vendor's library reaches 73), 8, 8, 10 280 -> 19
 // us, 4, 4, 10 131 -> 16 us, 12, 12, 2 77 -> 45 us; complex64 12, 13, 3 260 ->
 // 56 us (4.8 TB/s, HBM), 6, 6, 8 40 -> 10 us.  64 x 32 outputs a wave need 408

@@ -103,10 +103,11 @@ inline bool dense_uses_mfma(int k, int nloc, int mfma_min_k)
     return mfma_min_k >= 4 && k >= mfma_min_k && nloc >= k + 4;
 }
 
-// Staged sweep: nops dense blocks (k = 4 or 5, complex64) applied to LDS
-// tiles in one HBM pass.  pos[o] / mats[o]: block o's positions and device
+// Staged sweep: nops dense blocks (k = 4 or 5) applied to LDS tiles in one
+// HBM pass.  pos[o] / mats[o]: block o's positions and device
 // matrix.  The tile (positions 0..3 and every target) is widened with free
-// low positions up to t_max (<= 13) within the LDS budget.  Fails
+// low positions up to t_max (at most 14, complex128 13) within the LDS budget.
+// Fails
 // (hipErrorInvalidValue) when the targets alone exceed t_max positions or
 // the LDS budget; *t_out receives the tile width used.  from_e0: the input
 // is |0...0> and is not read (the pass writes every amplitude).  norm_out
@@ -121,7 +122,7 @@ inline bool dense_uses_mfma(int k, int nloc, int mfma_min_k)
 // *amps_out: amplitudes visited.  lone_t: tile limit of a pass of one 5-qubit
 // block on a large state (0: t_max; split-fp16 form).
 // dtype 0: complex64 (fp32 or split-fp16 form); 1: complex128 (FP64 form,
-// eight waves per CU, tiles of 9..13 positions).
+// up to eight waves per CU, tiles of 9..13 positions).
 int stage_lds_bytes(int t, int nops, const int* ks, int dtype = 0);
 // LDS budget of a tile of t positions (complex64: 80 KiB up to 13, two
 // workgroups per CU; 160 KiB at 14, one workgroup per CU; complex128:

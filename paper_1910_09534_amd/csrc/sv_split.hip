@@ -259,8 +259,9 @@ __device__ __forceinline__ uint32_t own(uint32_t at)
 // lanes of a workgroup for a tile of t positions
 constexpr int split_lanes(int t) { return t <= 10 ? 64 : 1 << (t - 4); }
 
-// Sixteen waves per CU (four per SIMD, 128 VGPRs each) whatever the tile:
-// one workgroup of 1024 lanes at t = 14, two of 512 at 13, and so on.
+// Sixteen waves per CU (four per SIMD, 128 VGPRs each): one workgroup of 1024
+// lanes at t = 14, two of 512 at 13, and so on, as far as their matrices leave
+// the LDS room; eight waves at most at t = 9 and 10, of one wave each.
 // K0, P0: the first block's width and whether position 0 is one of its
 // targets; ONE: it is the only one.  (Compile-time choices: the prefetched
 // operands then stay in one set of registers round the tile loop, where

@@ -7,11 +7,12 @@
 // (unitary complex64 blocks, the default) is in sv_split.hip, the FP64 form
 // (complex128) in sv_stage64.hip.
 //
-// A stage is a run of consecutive dense blocks (k = 4 or 5, complex64) whose
-// target positions, together with positions 0..3, fit in t <= 13 tile
-// positions P[0] < ... < P[t-1] (P[0..3] = 0..3; free low positions widen
-// the tile to 13 when the LDS budget allows).  A tile is the 2^t amplitudes whose other bits equal the
-// tile id.  A persistent workgroup (256 lanes) loops over tiles:
+// A stage is a run of consecutive dense blocks (k = 4 or 5) whose target
+// positions, together with positions 0..3, fit in t <= 14 tile positions
+// (complex128: 13) P[0] < ... < P[t-1] (P[0..3] = 0..3; free low positions widen
+// the tile as far as its limit and the LDS budget allow).  A tile is the 2^t
+// amplitudes whose other bits equal the tile id.  In the fp32 form a persistent
+// workgroup (256 lanes, 512 at t = 14) loops over tiles:
 //   1. the next tile's loads are issued (into registers; each lane holds
 //      pairs of adjacent amplitudes, 16 bytes per access: position 0 is
 //      always a tile position);
@@ -373,8 +374,8 @@ int stage_lds_bytes(int t, int nops, const int* ks, int dtype)
     return tile_f4 * 16 + scalars * 4;
 }
 
-// LDS a tile of t positions may use: complex64 as above; complex128 always
-// the whole CU (one 512-lane workgroup)
+// LDS a tile of t positions may use: complex64 as above; complex128 up to the
+// whole CU (one workgroup of 512 lanes at t = 13; narrower tiles share it)
 static inline int stage_lds_limit_dt(int t, int dtype) { return dtype ? kStageMaxLds14 : stage_lds_limit_t(t); }
 
 // the variant for a tile of t positions (9..14), 64-bit lane offsets, and
@@ -457,11 +458,10 @@ int stage_lds_limit(int t, int dtype)
 // Tile positions of a staged pass, ascending, into P (returns t, or -1 when
 // the run does not fit): 0..3 plus every target, widened with the lowest
 // free positions to the widest tile within t_max that the LDS holds (a
-// 14-position tile: one workgroup per CU; 13 and less: two or more 256-lane
-// ones).  Wider tiles mean more 16-group units per wave and longer
-// contiguous runs in memory: on the 30-qubit headline, widening to 14
-// wherever it fits measured 35.2-35.5 ms per step against 36.4 when tiles
-// widened to 13 at most.  Only positions inside the support widen it: one
+// 14-position tile: one workgroup per CU; 13 and less: two or more).  Wider
+// tiles mean longer contiguous runs in memory: with every block of a pass on
+// the LDS tile, before the form of sv_split.hip, widening to 14 wherever it
+// fits took the 30-qubit depth-14 circuit from 36.4 to 35.2-35.5 ms.  Only positions inside the support widen it: one
 // outside would double the amplitudes visited (beyond the 9 the kernel
 // needs).
 static int stage_positions(int nloc, int nops, const int* ks, const int* const* pos, int t_max,

@@ -142,7 +142,9 @@ __device__ __forceinline__ void apply64(uint32_t image, int lane, Get get, Out o
 // lanes of a workgroup for a tile of t positions
 constexpr int stage64_lanes(int t) { return t <= 10 ? 64 : 1 << (t - 4); }
 
-// Eight waves per CU (two per SIMD, 256 VGPRs each) whatever the tile.  K0:
+// Up to eight waves per CU (two per SIMD, 256 VGPRs each): one workgroup of 512
+// lanes at t = 13, two of 256 at 12 where two tiles and their matrices fit the
+// LDS (four 4-qubit blocks do not: four waves), and so on.  K0:
 // the first block's width; ONE: it is the only one.  (Compile-time choices, so
 // that the operands in flight stay in one set of registers round the loop.)
 template <int TW, bool ZERO, int K0, bool ONE>

@@ -269,10 +269,12 @@ def _lds_limit(t: int) -> int:
 
 
 # Widest tile per state: 14 positions for complex64 (one workgroup
-# per CU, fewer passes).  In the split-fp16 form, the default, it measured
-# faster at every size: 36.2-36.4 against 39.4-40.5 ms per 30-qubit step
-# (14 instead of 17 passes), batches of 20-28 qubits tuned to 14 from 23
-# qubits.  The fp32 form (SV_OPT_SPLIT 0) measured slower with 14 at 2^30
+# per CU, fewer passes).  In the split-fp16 form, the default, with every
+# block on the LDS tile it measured faster at every size: 36.2-36.4 against
+# 39.4-40.5 ms per 30-qubit step (14 instead of 17 passes), batches of 20-28
+# qubits tuned to 14 from 23 qubits (not measured again for the passes that
+# take their first and last block's amplitudes straight from and to memory).
+# The fp32 form (SV_OPT_SPLIT 0) measured slower with 14 at 2^30
 # amplitudes (45.8 against 44.6 ms per step), where two workgroups per CU
 # overlap its longer block work better; such callers pass 13.  Complex128
 # tiles hold at most 13 positions.
@@ -391,11 +393,13 @@ def order_for_staging(ops: Sequence["Op"], pos_of=None, tmax: Optional[int] = No
 # and a fixed part plus a cost per block.  Only the ranking of candidate
 # plans uses these figures.  Two forms of the staged kernel:
 #  * "split" (the library's default, SV_OPT_SPLIT 1): products on the fp16
-#    matrix cores; a block costs its LDS round trip, split and barrier more
-#    than its matrix-core work (least squares over 80 measured single
-#    passes on a dense 30-qubit state, tile limits 12..14, 2..8 blocks:
-#    memory 3.5, fixed 0.55, per 4-qubit block 0.83, per 5-qubit block 0.95;
-#    rms error 0.24 ms);
+#    matrix cores; least squares over 80 single passes on a dense 30-qubit
+#    state, tile limits 12..14, 2..8 blocks: memory 3.5, fixed 0.55, per
+#    4-qubit block 0.83, per 5-qubit block 0.95; rms error 0.24 ms.  Taken
+#    when every block of a pass made a trip through LDS; the present passes
+#    make one less at either end and are bound by memory up to four blocks
+#    (3.3-3.9 ms by where the tile's positions lie), so the figures price
+#    blocks higher than they are; not fitted again;
 #  * "fp32" (SV_OPT_SPLIT 0): the fp32 matrix cores bound the pass (fitted
 #    to measured 30-qubit step times of 31 aggregations: memory 3.35, fixed
 #    1.475, per 5-qubit block 1.78, per 4-qubit block 1.10).
@@ -405,7 +409,7 @@ def order_for_staging(ops: Sequence["Op"], pos_of=None, tmax: Optional[int] = No
 # blocks in 13 passes), and planned for passes over the whole state the
 # split fit's plan (33 blocks, 29 of them 5-qubit, in 13 passes) runs
 # 48.0-48.9 ms per step against 50.5-51.4 for the fp32 figures' (37
-# blocks, 11 of them 5-qubit).  With 13-position tiles the fp32 figures
+# blocks, 11 of them 5-qubit), as every block made its trip then.  With 13-position tiles the fp32 figures
 # had ranked better (0.2-1.0 ms on that circuit): the split fit's max()
 # prices blocks under the memory time as free, which they are not quite.
 SWEEP_MS = {1: 2.9, 2: 2.9, 3: 3.4, 4: 3.5, 5: 3.57, 6: 3.7}

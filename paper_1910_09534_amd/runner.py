@@ -124,8 +124,8 @@ REDUCE_THREADS = 8
 
 def run_batch(circuits, bits_list, dtype="c64", kmax=5, mfma_min_k=4, graph: bool = True,
               repeats: int = 1, plans=None, staged: bool = False, stage_t=None) -> Dict[str, object]:
-    """Many independent circuits as one batched execution (one graph launch
-    per run).  kmax / mfma_min_k / stage_t: an int, or a dict n -> value
+    """Many independent circuits as one batched execution (graph: recorded
+    graphs side by side).  kmax / mfma_min_k / stage_t: an int, or a dict n -> value
     (autotuned).  staged (complex64): each state's runs of 4/5-qubit blocks
     go through staged passes (tile limit stage_t, default
     planner.stage_tmax(n)), planned for them.  Each repeat resets every
