@@ -40,9 +40,9 @@
 //
 // What bounds it: memory.  On the 30-qubit depth-14 circuit the full passes
 // (16 GiB, 2 to 4 blocks) take 3.3-3.9 ms, 4.4-5.2 TB/s, with the matrix cores
-// busy 18-40 %, VALU issue 20-40 % and the LDS 8-28 % (0-0.2 conflict cycles
-// an access); a kernel that only reads and writes the same tiles takes
-// 3.0-3.9 ms, the more the further apart the tile's positions lie.  The
+// busy 19-42 %, VALU issue 21-43 % and the LDS 9-22 % of the time (0-0.12
+// conflict cycles an access); a kernel that only reads and writes tiles of the
+// same kind takes 3.1-4.0 ms, by where the tile's positions lie.  The
 // circuit takes 26.1 ms against 29.3 ms with every block on the LDS tile
 // (park, n blocks, store: 3.6-4.1 ms a pass, padded tile, 0.2-0.3 conflict
 // cycles an access); sixteen circuits of 20 to 24 qubits 5.2 against 5.8 ms.
