@@ -129,8 +129,8 @@ int stage_lds_bytes(int t, int nops, const int* ks, int dtype = 0);
 // 160 KiB).  The sizes are those of padded tiles, as the fp32 form has them;
 // the other two forms' take no more.
 int stage_lds_limit(int t, int dtype = 0);
-// Sets the staged kernels' LDS attribute for every tile width (idempotent;
-// launch_stage does it on first use, graph capture needs it beforehand).
+// Sets every staged kernel's LDS attribute (idempotent; launch_stage does it
+// for the kernel it launches, graph capture needs it beforehand).
 hipError_t stage_prepare();
 // Widest tile the device runs: complex64 14, or 13 where a workgroup cannot
 // have the whole LDS of a CU; complex128 13, or 0 (no staged passes) there.
@@ -147,11 +147,14 @@ hipError_t launch_stage(hipStream_t st, void* psi, int nloc, int nops, const int
 // with the tile chosen: positions P[0..t), the tiles' mask over the other
 // positions, newmask = the tile positions whose elements are zero but may
 // hold older values, park: every tile through LDS on both sides.
-// split_prepare: LDS attribute of a tile width's kernels.
+// split_prepare: LDS attribute of one of a tile width's kernels (v: zeroing,
+// first block of 5 qubits, position 0 among its targets, only block; 16: a
+// parking step first), once.
 hipError_t launch_split(hipStream_t st, void* psi, int t, const int* P, int nops, const int* ks,
                         const int* const* pos, const void* const* mats, uint64_t tiles, uint64_t tmask,
                         uint64_t newmask, bool from_e0, double* norm_out, int* norm_blocks, int split_exp, bool park);
-hipError_t split_prepare(int t, int lds);
+constexpr int kSplitForms = 18;
+hipError_t split_prepare(int t, int v);
 // Tile limit of a pass of one block on 2^bits amplitudes (at most t_max; 5 qubits
 // on a large state: wide_max) and whether its tiles are parked in LDS on both sides.
 struct SplitLone {
@@ -163,7 +166,8 @@ SplitLone split_lone(int k, const int* pos, int bits, int t_max, int wide_max);
 hipError_t launch_stage64(hipStream_t st, void* psi, int t, const int* P, int nops, const int* ks,
                           const int* const* pos, const void* const* mats, uint64_t tiles, uint64_t tmask,
                           uint64_t newmask, bool from_e0, double* norm_out, int* norm_blocks);
-hipError_t stage64_prepare(int lds);
+constexpr int kStage64Forms = 8;             // zeroing, first block of 5 qubits, only block
+hipError_t stage64_prepare(int t, int v);
 // Exponent e of the split-fp16 form's tile scale 2^e for a run whose
 // blocks are all unitary and whose state norm stays below bound: the
 // largest e with 2^e bound <= 2^15 (-100..100); kNoSplit when bound is not

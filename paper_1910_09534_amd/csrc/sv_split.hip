@@ -46,6 +46,7 @@
 // circuit takes 26.1 ms against 29.3 ms with every block on the LDS tile
 // (park, n blocks, store: 3.6-4.1 ms a pass, padded tile, 0.2-0.3 conflict
 // cycles an access); sixteen circuits of 20 to 24 qubits 5.2 against 5.8 ms.
+#include <atomic>
 #include <cmath>
 
 #include "sv_device.h"
@@ -653,15 +654,16 @@ SplitLone split_lone(int k, const int* pos, int bits, int t_max, int wide_max)
     return {t_max < 12 ? t_max : 12, false};
 }
 
-hipError_t split_prepare(int t, int lds)
+hipError_t split_prepare(int t, int v)
 {
-    for (int v = 0; v < 18; ++v) {
-        const SplitKernel kern = v < 16 ? split_kernel(t, v & 1, v & 2 ? 5 : 4, (v >> 2) & 1, v & 8)
-                                        : split_kernel(t, v & 1, 0, 0, false);
-        const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    static std::atomic<bool> done[6][kSplitForms];
+    if (done[t - 9][v]) return hipSuccess;
+    const SplitKernel kern = v < 16 ? split_kernel(t, v & 1, v & 2 ? 5 : 4, (v >> 2) & 1, v & 8)
+                                    : split_kernel(t, v & 1, 0, 0, false);
+    const hipError_t e =
+        hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, stage_lds_limit(t));
+    if (e == hipSuccess) done[t - 9][v] = true;
+    return e;
 }
 
 hipError_t launch_split(hipStream_t st, void* psi, int t, const int* P, int nops, const int* ks,
@@ -749,7 +751,11 @@ hipError_t launch_split(hipStream_t st, void* psi, int t, const int* P, int nops
     const uint64_t cap = 256ull * per_cu;
     if (grid > cap) grid = cap;
     a.tstep = spread_bits(grid, a.tmask);
-    hipLaunchKernelGGL(split_kernel(t, newmask != 0, a.op[0].k, a.op[0].pair, steps == 1), dim3((unsigned)grid), dim3(nt), lds, st, (float2*)psi, a);
+    const bool zero = newmask != 0, one = steps == 1;
+    const int k0 = a.op[0].k, pair0 = a.op[0].pair;
+    const hipError_t e = split_prepare(t, (k0 ? (k0 == 5 ? 2 : 0) | pair0 << 2 | (one ? 8 : 0) : 16) | (zero ? 1 : 0));
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(split_kernel(t, zero, k0, pair0, one), dim3((unsigned)grid), dim3(nt), lds, st, (float2*)psi, a);
     if (norm_blocks) *norm_blocks = norm_out ? (int)grid : 0;
     return hipGetLastError();
 }

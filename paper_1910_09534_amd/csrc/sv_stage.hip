@@ -398,37 +398,38 @@ static void (*stage_kernel(int t, bool wide, bool zero))(float2*, StageK)
     return nullptr;
 }
 
-// 14-position tiles need the whole LDS of a CU for one workgroup; where the
-// device refuses that, tiles stop at 13 positions (and complex128 states
-// take no staged passes)
-static std::atomic<bool> g_stage14{false};
-static std::atomic<bool> g_stage64{false};
+// LDS limit of one variant of the fp32 form (v: 64-bit lane offsets, zeroing)
+static hipError_t stage32_prepare(int t, int v)
+{
+    static std::atomic<bool> done[6][4];
+    if (done[t - 9][v]) return hipSuccess;
+    const hipError_t e = hipFuncSetAttribute((const void*)stage_kernel(t, v & 1, v & 2),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, stage_lds_limit_t(t));
+    if (e == hipSuccess) done[t - 9][v] = true;
+    return e;
+}
 
+// Launches set their own kernel's LDS limit on its first use; all of them at
+// once (some 170 variants, 4 ms) only ahead of a capture.
 hipError_t stage_prepare()
 {
     static std::atomic<bool> done{false};
     if (done) return hipSuccess;
-    for (int t = 9; t <= 13; ++t) {
+    for (int t = 9; t <= stage_max_t(0); ++t) {
         for (int v = 0; v < 4; ++v) {
-            void (*k)(float2*, StageK) = stage_kernel(t, v & 1, v & 2);
-            const hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                     kStageMaxLds);
+            const hipError_t e = stage32_prepare(t, v);
             if (e != hipSuccess) return e;
         }
-        const hipError_t e = split_prepare(t, kStageMaxLds);
-        if (e != hipSuccess) return e;
+        for (int v = 0; v < kSplitForms; ++v) {
+            const hipError_t e = split_prepare(t, v);
+            if (e != hipSuccess) return e;
+        }
     }
-    bool ok14 = split_prepare(14, kStageMaxLds14) == hipSuccess;
-    for (int v = 0; v < 4 && ok14; ++v) {
-        void (*k)(float2*, StageK) = stage_kernel(14, v & 1, v & 2);
-        ok14 = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, kStageMaxLds14) ==
-               hipSuccess;
-    }
-    if (!ok14) (void)hipGetLastError();
-    g_stage14 = ok14;
-    const bool ok64 = stage64_prepare(kStageMaxLds14) == hipSuccess;
-    if (!ok64) (void)hipGetLastError();
-    g_stage64 = ok64;
+    for (int t = 9; t <= stage_max_t(1); ++t)
+        for (int v = 0; v < kStage64Forms; ++v) {
+            const hipError_t e = stage64_prepare(t, v);
+            if (e != hipSuccess) return e;
+        }
     done = true;
     return hipSuccess;
 }
@@ -443,11 +444,22 @@ int split_exponent(double bound)
     return e < -100 ? kNoSplit : (e > 100 ? 100 : e);
 }
 
+// 14-position tiles need the whole LDS of a CU for one workgroup; where the
+// device refuses that, tiles stop at 13 positions (and complex128 states
+// take no staged passes)
 int stage_max_t(int dtype)
 {
-    if (stage_prepare() != hipSuccess) return dtype ? 0 : 13;
-    if (dtype) return g_stage64 ? 13 : 0;
-    return g_stage14 ? kStageMaxT : 13;
+    static std::atomic<int> found[2];                     // 0: not asked yet
+    const int d = dtype ? 1 : 0;
+    int t = found[d];
+    if (t == 0) {
+        const bool ok = (d ? stage64_prepare(13, 0) : split_prepare(kStageMaxT, 0)) == hipSuccess;
+        t = d ? (ok ? 13 : -1) : (ok ? kStageMaxT : 13);
+        // (refused, if a narrow tile is not: else asked again)
+        if (ok || split_prepare(9, 0) == hipSuccess) found[d] = t;
+        if (!ok) (void)hipGetLastError();
+    }
+    return t < 0 ? 0 : t;
 }
 
 int stage_lds_limit(int t, int dtype)
@@ -558,20 +570,16 @@ hipError_t launch_stage(hipStream_t st, void* psi, int nloc, int nops, const int
     for (int b = 0; b < t; ++b)
         if ((newmask >> P[b]) & 1) a.newmask_t |= 1u << b;
     if (split) {
-        hipError_t e = stage_prepare();
-        if (e != hipSuccess) return e;
-        e = launch_split(st, psi, t, P, nops, ks, pos, mats, a.tiles, a.tmask, newmask, from_e0, norm_out,
-                         norm_blocks, split_exp, park);
+        const hipError_t e = launch_split(st, psi, t, P, nops, ks, pos, mats, a.tiles, a.tmask, newmask, from_e0,
+                                          norm_out, norm_blocks, split_exp, park);
         if (t_out) *t_out = t;
         if (tile_mask_out) *tile_mask_out = pmask;
         if (amps_out) *amps_out = a.tiles << t;
         return e;
     }
     if (dtype) {
-        hipError_t e = stage_prepare();
-        if (e != hipSuccess) return e;
-        e = launch_stage64(st, psi, t, P, nops, ks, pos, mats, a.tiles, a.tmask, newmask, from_e0, norm_out,
-                           norm_blocks);
+        const hipError_t e = launch_stage64(st, psi, t, P, nops, ks, pos, mats, a.tiles, a.tmask, newmask, from_e0,
+                                            norm_out, norm_blocks);
         if (t_out) *t_out = t;
         if (tile_mask_out) *tile_mask_out = pmask;
         if (amps_out) *amps_out = a.tiles << t;
@@ -615,7 +623,7 @@ hipError_t launch_stage(hipStream_t st, void* psi, int nloc, int nops, const int
     void (*kern)(float2*, StageK) = stage_kernel(t, wide, a.newmask_t != 0);
     if (!kern) return hipErrorInvalidValue;
     {
-        const hipError_t e = stage_prepare();
+        const hipError_t e = stage32_prepare(t, (wide ? 1 : 0) | (a.newmask_t ? 2 : 0));
         if (e != hipSuccess) return e;
     }
     // persistent: as many workgroups as are resident (LDS-limited, at most 4

@@ -33,6 +33,7 @@
 // LDS.  Amplitude i of the tile sits at i ^ (i >> 3 & 7) ^ (i >> 6 & 7) ^
 // (i >> 9 & 7) ^ (i >> 12 & 7): linear over GF(2) and without padding, as in
 // the split-fp16 form.
+#include <atomic>
 #include <type_traits>
 
 #include "sv_device.h"
@@ -401,15 +402,15 @@ uint32_t slot64(int b)
 
 }  // namespace
 
-hipError_t stage64_prepare(int lds)
+hipError_t stage64_prepare(int t, int v)
 {
-    for (int t = 9; t <= 13; ++t)
-        for (int v = 0; v < 8; ++v) {
-            const hipError_t e = hipFuncSetAttribute((const void*)stage64_kernel(t, v & 1, v & 2 ? 5 : 4, v & 4),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-            if (e != hipSuccess) return e;
-        }
-    return hipSuccess;
+    static std::atomic<bool> done[5][kStage64Forms];
+    if (done[t - 9][v]) return hipSuccess;
+    const hipError_t e =
+        hipFuncSetAttribute((const void*)stage64_kernel(t, v & 1, v & 2 ? 5 : 4, v & 4),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, stage_lds_limit(t, 1));
+    if (e == hipSuccess) done[t - 9][v] = true;
+    return e;
 }
 
 hipError_t launch_stage64(hipStream_t st, void* psi, int t, const int* P, int nops, const int* ks,
@@ -482,8 +483,11 @@ hipError_t launch_stage64(hipStream_t st, void* psi, int t, const int* P, int no
     const uint64_t cap = 256ull * per_cu;
     if (grid > cap) grid = cap;
     a.tstep = spread_bits(grid, a.tmask);
-    hipLaunchKernelGGL(stage64_kernel(t, newmask != 0, a.op[0].k, nops == 1), dim3((unsigned)grid), dim3(nt), lds, st,
-                       (double2*)psi, a);
+    const bool zero = newmask != 0, one = nops == 1;
+    const int k0 = a.op[0].k;
+    const hipError_t e = stage64_prepare(t, (zero ? 1 : 0) | (k0 == 5 ? 2 : 0) | (one ? 4 : 0));
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(stage64_kernel(t, zero, k0, one), dim3((unsigned)grid), dim3(nt), lds, st, (double2*)psi, a);
     if (norm_blocks) *norm_blocks = norm_out ? (int)grid : 0;
     return hipGetLastError();
 }

@@ -9,6 +9,7 @@
 //   fake_log            one line per call, since fake_clear
 //   fake_undone         work items launched and not known to be complete
 //   fake_bad_frees      buffers freed while work was outstanding
+//   fake_lds_limit      dynamic LDS that a kernel may be given
 // Two kernels act on memory: k_upload copies, and k_reduce counts its ticket
 // up and leaves it so when the call's copies fail afterwards (an interrupted
 // reduction); a ticket that is not zero at its launch is logged.
@@ -41,6 +42,8 @@ long g_next = 1, g_bad_frees = 0;
 std::map<std::string, int> g_fail;
 std::set<std::string> g_fail_always;
 std::map<const void*, std::string> g_kernels;
+std::map<const void*, int> g_lds;      // dynamic LDS a kernel may use (64 KiB unless set)
+int g_lds_limit = 160 * 1024;          // ... and that the device has
 std::map<const void*, size_t> g_vars;
 std::map<const void*, void*> g_var_mem;
 std::map<void*, size_t> g_alloc;
@@ -119,6 +122,7 @@ const char* fake_log() { return g_log.c_str(); }
 void fake_clear() { g_log.clear(); }
 long fake_undone() { return (long)g_undone.size(); }
 long fake_bad_frees() { return g_bad_frees; }
+void fake_lds_limit(int bytes) { g_lds_limit = bytes; }
 void fake_fail(const char* api, int n)
 {
     if (n > 0) g_fail[api] = n;
@@ -163,7 +167,8 @@ hipError_t hipLaunchKernel(const void* f, dim3 g, dim3 b, void** args, size_t sh
     const uint64_t lim = 1ull << 32;
     // work items per dimension stay below 2^32, workgroups take at most 1024 lanes
     if (!g.x || !g.y || !g.z || (uint64_t)g.x * b.x >= lim || (uint64_t)g.y * b.y >= lim ||
-        (uint64_t)g.z * b.z >= lim || b.x * b.y * b.z > 1024 || shmem > 160 * 1024) {
+        (uint64_t)g.z * b.z >= lim || b.x * b.y * b.z > 1024 ||
+        shmem > (size_t)(g_lds.count(f) ? g_lds[f] : 64 * 1024)) {
         note("refused " + name + line);
         return fail(hipErrorInvalidConfiguration);
     }
@@ -183,7 +188,13 @@ hipError_t hipLaunchKernel(const void* f, dim3 g, dim3 b, void** args, size_t sh
     work(of(st));
     return hipSuccess;
 }
-hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
+hipError_t hipFuncSetAttribute(const void* f, hipFuncAttribute, int value)
+{
+    note("attribute " + g_kernels[f]);
+    if (value > g_lds_limit) return fail(hipErrorInvalidValue);
+    g_lds[f] = value;
+    return hipSuccess;
+}
 
 // ---- memory ------------------------------------------------------------------
 hipError_t hipMalloc(void** p, size_t n)

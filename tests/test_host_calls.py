@@ -284,3 +284,55 @@ def test_amplitude_bound_follows_reductions(fake_hip, where):
     sv.reset(h)
     assert sv.stage_forms(h)["amp_bound"] == 1.0
     """)
+
+
+STAGED = """
+def passes(h, n, dtype, widths, count):
+    r = np.random.default_rng(n)
+    for i in range(count):
+        k = widths[i % len(widths)]
+        sv.apply_fused(h, [int(q) for q in r.choice(min(n, 9), k, replace=False)], unitary(k, i), dtype)
+    sv.sync_state(h)
+"""
+
+
+@pytest.mark.parametrize("limit", [160, 80])
+def test_staged_kernels_get_their_lds(fake_hip, limit):
+    """A staged kernel's LDS limit is set before its first launch, alone and in
+    a captured batch, and not those of all the others; where the device gives
+    a workgroup 80 KiB only, tiles stop at 13 positions and complex128 states
+    take single sweeps."""
+    run(fake_hip, STAGED + textwrap.dedent(f"""
+    F.fake_lds_limit({limit} * 1024)
+    for dtype in ("c64", "c128"):
+        for n in (9, 12, 14, 16, 28):
+            for stage in (9, 10, 12, 13, 14):
+                for split in (1, 0):
+                    h = sv.create_state(n, 0, dtype)
+                    sv.set_option(h, sv.SV_OPT_STAGE, stage)
+                    sv.set_option(h, sv.SV_OPT_SPLIT, split)
+                    F.fake_clear()
+                    for count in (1, 2, 5):
+                        passes(h, n, dtype, (4, 5), count)
+                        sv.reset(h)
+                        passes(h, n, dtype, (5, 4), count)
+                        sv.reduce_slices(h, np.arange(4, dtype=np.uint64))
+                    lines = log()
+                    assert not [x for x in lines if x.startswith("refused")], (dtype, n, stage, split)
+                    assert sum(x.startswith("attribute") for x in lines) <= 24
+                    staged = [x for x in lines if x.startswith("launch") and ("k_split" in x or "k_stage" in x)]
+                    assert bool(staged) == (dtype == "c64" or {limit} == 160), (dtype, n, stage, split)
+                    sv.destroy_state(h)
+    for n in (12, 20, 23):
+        h = sv.create_state(n, 0, "c64")
+        for i, k in enumerate((5, 5, 4, 5)):
+            sv.apply_fused(h, list(range(i, i + k)), unitary(k, i), "c64")
+        F.fake_clear()
+        b = sv.batch_prepare([h], graph=True)
+        lines = log()
+        capture = [i for i, x in enumerate(lines) if x.startswith("capture")]
+        assert capture and not any(x.startswith("attribute") for x in lines[capture[0]:])
+        assert not any(x.startswith("refused") for x in lines)
+        sv.batch_launch(b)
+        sv.batch_destroy(b)
+    """))
